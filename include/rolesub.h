@@ -136,8 +136,9 @@ rolesub_status rolesub_rotate_values(const rolesub_dims* dims, rolesub_dtype dty
  *   idx        [B,T,G] uint8 or NULL: kept group ids ascending, then 0xFF.
  *   count      [B,T]   uint8 or NULL: K_i actually kept.
  *   workspace  device scratch of at least rolesub_route_workspace_size()
- *              bytes (may be NULL if that size is 0). Nothing in it needs
- *              clearing; calls sharing one workspace must not overlap.
+ *              bytes (may be NULL if that size is 0; it does not fall as B
+ *              or T grows). Nothing in it needs clearing; calls sharing one
+ *              workspace must not overlap.
  * The environment variable ROLESUB_SK_POLLS (0..1000, default 32), read at
  * each call, bounds how long the first workgroup of a split-K router tile
  * waits for the second to share the tile's epilogue; the outputs are the
@@ -154,17 +155,18 @@ rolesub_status rolesub_route(const rolesub_dims* dims, rolesub_dtype dtype,
  * rolesub_route_noalloc: rolesub_route without a workspace argument, for
  * callers that cannot allocate device memory (code under stream capture,
  * serving loops that forbid allocation). Same arguments as rolesub_route and
- * the same results, bit for bit (the bf16 MLP2 router runs as its single
- * kernel here, which sums the same terms in the same order as the split-K
- * form rolesub_route uses); the route workspace is a file-scope device array of
+ * the same results, bit for bit (where rolesub_route uses the split-K form of
+ * the bf16 MLP2 router this call runs its single kernel, which sums the same
+ * terms in the same order; elsewhere both run the same kernels, this call over
+ * ranges of samples where the array asks for it); the route workspace is a file-scope device array of
  * ROLESUB_ROUTE_NOALLOC_MAX_BYTES that each device holds until the process
  * ends (its address is looked up once per device, with that device current).
  * Nothing is allocated or freed, by the library or any routine it calls.
  *   - Calls whose route workspace exceeds the maximum return
  *     ROLESUB_ERR_UNSUPPORTED before anything is enqueued (with d = 4096 and
  *     Hr = 128: more than 334 samples). That workspace is
- *     rolesub_route_workspace_size() less the split-K partial products and
- *     tile counters, which the single kernel does not use.
+ *     rolesub_route_workspace_size() less the areas of partial products, which
+ *     the call sizes by the room left.
  *   - stream must belong to the current device (else ROLESUB_ERR_INVALID_ARG).
  *   - Every call on one device shares that device's array and overwrites it
  *     (every byte the kernels read is written earlier in the same call, so

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "librolesub.so")
-SOURCES = ["rolesub_api.hip", "k_route.hip", "k_rotate.hip", "k_pack.hip", "k_attend.hip", "k_retain.hip",
+SOURCES = ["rolesub_api.hip", "k_route.hip", "k_route_tile.hip", "k_rotate.hip", "k_pack.hip", "k_attend.hip", "k_retain.hip",
            "k_alloc.hip", "k_full.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -219,10 +219,10 @@ __global__ __launch_bounds__(256) void k_route_cbsum(RouteParams p, int ncb) {
 // Per-sample language term and folded role term. 1D grid:
 //   blocks [0, B*nrb): 8 output rows of one sample (2 per wave),
 //     MLP2:     cb[b][j] = W1[j, d+d_e : 2d+d_e] . hbar[b] + b1[j]
-//     ADDITIVE: cb[b][s] = alpha_lang (W_lang[s] . hbar[b] + b_lang[s])
+//     ADDITIVE: cb[b][s] = alpha_lang (W_lang[s] . hbar[b] + b_lang[s]) + b_tok[s]
 //   blocks [B*nrb, ...): F rows, one per wave,
 //     MLP2:     F[j][c] = W1[j, d : d+d_e] . E[c]      (so W1_e e = F a)
-//     ADDITIVE: F[s][c] = alpha_role W_role[s][c]
+//     (ADDITIVE: none; the two-kernel form folds its own role term)
 template <class T>
 __global__ __launch_bounds__(256) void k_route_proj(RouteParams p) {
   extern __shared__ float hs[];
@@ -276,10 +276,6 @@ __global__ __launch_bounds__(256) void k_route_proj(RouteParams p) {
           }
         }
       }
-    } else {
-      if (j >= p.G) return;
-      const T* Wro = static_cast<const T*>(p.W_role);
-      for (int c = lane; c < p.C; c += 64) p.F[j * p.C + c] = p.alpha_role * tof(Wro[j * p.C + c]);
     }
     return;
   }
@@ -344,7 +340,11 @@ __global__ __launch_bounds__(256) void k_route_proj(RouteParams p) {
       for (int k = lane; k < p.d; k += 64) acc += tof(wrow[k]) * hs[pos(k)];
     }
     acc = wave_sum(acc);
-    if (lane == 0) p.cb[static_cast<size_t>(b) * nout + j] = scale * (acc + bias);
+    if (lane == 0) {
+      float c = scale * (acc + bias);
+      if (p.kind != 0) c += tof(static_cast<const T*>(p.b_tok)[j]);
+      p.cb[static_cast<size_t>(b) * route_ld(nout) + j] = c;
+    }
   }
 }
 
@@ -465,90 +465,6 @@ __global__ __launch_bounds__(kSelTok) __attribute__((amdgpu_waves_per_eu(NP == 3
     for (int q = tid; q < nv; q += kSelTok)
       *reinterpret_cast<u32x4*>(out + 16 * q) = *reinterpret_cast<const u32x4*>(sidx + 16 * q);
     for (int e = nv * 16 + tid; e < nb; e += kSelTok) out[e] = sidx[e];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Generic router: one workgroup per token, vector ALU. Any shape, either
-// router kind; the f32 path and unusual bf16 shapes use it.
-template <class T>
-__global__ __launch_bounds__(256) void k_route_generic(RouteParams p) {
-  extern __shared__ float sh[];
-  __shared__ float a[64];
-  const int tid = threadIdx.x;
-  const size_t tok = blockIdx.x;
-  const int b = static_cast<int>(tok / p.T);
-  const int d = p.d, C = p.C, G = p.G;
-  const int nmain = p.kind == 0 ? p.Hr : G;
-  float* hs = sh;
-  float* dots = hs + d;
-  float* gl = dots + nmain + C;
-  float* gam = gl + (p.kind == 0 ? p.Hr : 0);
-  const T* h = static_cast<const T*>(p.h) + tok * d;
-  for (int k = tid; k < d; k += 256) hs[k] = tof(h[k]);
-  __syncthreads();
-  const size_t W1s = 2 * static_cast<size_t>(d) + p.d_e;
-  for (int o = tid; o < nmain + C; o += 256) {
-    const T* wrow;
-    if (o < nmain)
-      wrow = p.kind == 0 ? static_cast<const T*>(p.W1) + o * W1s
-                         : static_cast<const T*>(p.W_tok) + static_cast<size_t>(o) * d;
-    else
-      wrow = static_cast<const T*>(p.W_r) + static_cast<size_t>(o - nmain) * d;
-    float acc = 0.f;
-    for (int k = 0; k < d; ++k) acc += tof(wrow[k]) * hs[k];
-    dots[o] = acc;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    const T* br = static_cast<const T*>(p.b_r);
-    float mx = -INFINITY;
-    for (int c = 0; c < C; ++c) mx = fmaxf(mx, dots[nmain + c] + tof(br[c]));
-    float sm = 0.f;
-    for (int c = 0; c < C; ++c) {
-      a[c] = expf(dots[nmain + c] + tof(br[c]) - mx);
-      sm += a[c];
-    }
-    for (int c = 0; c < C; ++c) a[c] /= sm;
-    if (p.priority) {
-      const T* wp = static_cast<const T*>(p.w_pri);
-      float pr = 0.f;
-      for (int c = 0; c < C; ++c) pr = fmaf(tof(wp[c]), a[c], pr);
-      p.priority[tok] = pr;
-    }
-  }
-  __syncthreads();
-  if (p.kind == 0) {
-    for (int j = tid; j < p.Hr; j += 256) {
-      float x = dots[j] + p.cb[static_cast<size_t>(b) * p.Hr + j];
-      for (int c = 0; c < C; ++c) x += p.F[j * C + c] * a[c];
-      gl[j] = gelu_exact(x);
-    }
-    __syncthreads();
-    const T* W2 = static_cast<const T*>(p.W2);
-    const T* b2 = static_cast<const T*>(p.b2);
-    for (int s = tid; s < G; s += 256) {
-      float acc = 0.f;
-      for (int j = 0; j < p.Hr; ++j) acc += tof(W2[static_cast<size_t>(s) * p.Hr + j]) * gl[j];
-      gam[s] = acc + tof(b2[s]);
-    }
-  } else {
-    const T* bt = static_cast<const T*>(p.b_tok);
-    for (int s = tid; s < G; s += 256) {
-      float x = dots[s] + tof(bt[s]);
-      float r = 0.f;
-      for (int c = 0; c < C; ++c) r += p.F[s * C + c] * a[c];
-      gam[s] = x + r + p.cb[static_cast<size_t>(b) * G + s];
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float g[32];
-#pragma unroll
-    for (int s = 0; s < 32; ++s) g[s] = s < G ? gam[s] : 0.f;
-    if (p.mask) write_selection(p, tok, select_token<32>(p, g, p.types[tok]));
-    if (p.scores_out)
-      for (int s = 0; s < G; ++s) p.scores_out[tok * G + s] = gam[s];
   }
 }
 
@@ -728,7 +644,7 @@ __global__ __launch_bounds__(256) void k_route_mlp2_bf16(RouteParams p, int npcb
 #pragma unroll
   for (int c = 0; c < kRtNB - 1; ++c) issue(c);
   // the two halves of the hidden size are summed separately and added at the
-  // end, as the split-K form does; one loop per half keeps the first half's
+  // end, as the split-K and two-kernel forms do; one loop per half keeps the first half's
   // sums out of the loop-carried state of the second
   const int nlo = nch / 2;
   for (int c = 0; c < nlo; ++c) step(c);
@@ -830,10 +746,10 @@ __global__ __launch_bounds__(256) void k_route_mlp2_bf16(RouteParams p, int npcb
     }
   }
   float gam[GP];
-#pragma unroll
-  for (int s = 0; s < GP; ++s) gam[s] = 0.f;
+  // per block of 16 units, then over the blocks (as the two-kernel form's waves)
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
+    float gm[GP];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int j = 16 * m + 4 * g4 + i;
@@ -842,12 +758,12 @@ __global__ __launch_bounds__(256) void k_route_mlp2_bf16(RouteParams p, int npcb
 #pragma unroll
       for (int s4 = 0; s4 < GP / 4; ++s4) {
         const f32x4 w2 = wr[s4];
-        gam[4 * s4] += w2[0] * gl;
-        gam[4 * s4 + 1] += w2[1] * gl;
-        gam[4 * s4 + 2] += w2[2] * gl;
-        gam[4 * s4 + 3] += w2[3] * gl;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gm[4 * s4 + e] = i ? fmaf(w2[e], gl, gm[4 * s4 + e]) : w2[e] * gl;
       }
     }
+#pragma unroll
+    for (int s = 0; s < GP; ++s) gam[s] = m ? gam[s] + gm[s] : gm[s];
   }
   int n_above = 0;
 #pragma unroll
@@ -1198,10 +1114,10 @@ __global__ __launch_bounds__(64 * kSkW) void k_route_mlp2_sk(RouteParams p, int 
     }
   }
   float gam[GP];
-#pragma unroll
-  for (int s = 0; s < GP; ++s) gam[s] = 0.f;
+  // per block of 16 units, then over the blocks (as the two-kernel form's waves)
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
+    float gm[GP];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int j = 16 * m + 4 * g4 + i;
@@ -1210,12 +1126,12 @@ __global__ __launch_bounds__(64 * kSkW) void k_route_mlp2_sk(RouteParams p, int 
 #pragma unroll
       for (int s4 = 0; s4 < GP / 4; ++s4) {
         const f32x4 w2 = wr[s4];
-        gam[4 * s4] += w2[0] * gl;
-        gam[4 * s4 + 1] += w2[1] * gl;
-        gam[4 * s4 + 2] += w2[2] * gl;
-        gam[4 * s4 + 3] += w2[3] * gl;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) gm[4 * s4 + e] = i ? fmaf(w2[e], gl, gm[4 * s4 + e]) : w2[e] * gl;
       }
     }
+#pragma unroll
+    for (int s = 0; s < GP; ++s) gam[s] = m ? gam[s] + gm[s] : gm[s];
   }
   int n_above = 0;
 #pragma unroll
@@ -1269,49 +1185,71 @@ __global__ __launch_bounds__(64 * kSkW) void k_route_mlp2_sk(RouteParams p, int 
 }
 }  // namespace
 
+namespace {
+// Tokens up to which the two-kernel form is the faster one where the
+// one-kernel forms apply: at d = 4096, G = 8, 48 language tokens of 177, 21.6
+// against 31.8 us (1 prefix), 27 against 33.2 (16 prefixes), even at about 24
+// prefixes, where its pooling blocks and tiles no longer fit the chip together;
+// at d = 1024 17.4 against 28.6 (5 prefixes of 561). Both give the same bits.
+constexpr size_t kTileMaxTok = 3072;
+}  // namespace
+
+bool route_uses_tiles(int B, int T, int d, int G, int C, int Hr, int kind, bool bf16) {
+  const size_t ntok = static_cast<size_t>(B) * T;
+  const bool mfma_ok = bf16 && kind == 0 && Hr == 128 && C >= 1 && C <= 16 && G <= 32 && d % kRtKc == 0 &&
+                       ntok < (1u << 30);
+  return !mfma_ok || ntok <= kTileMaxTok;
+}
+
+void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s) {
+  const int vec = bf16 ? 8 : 4, ncb = (p.d + 64 * vec - 1) / (64 * vec);
+  const int nout = p.kind == 0 ? p.Hr : p.G;
+  const dim3 gpool(static_cast<unsigned>(p.B * ncb));
+  const dim3 gproj(static_cast<unsigned>(p.B * ((nout + 7) / 8) + (p.kind == 0 ? (nout + 3) / 4 : 0)));
+  const size_t shm = static_cast<size_t>(p.d) * sizeof(float);
+  if (bf16) {
+    hipLaunchKernelGGL((k_route_pool<rolesub::bf16, false>), gpool, dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_route_proj<rolesub::bf16>, gproj, dim3(256), shm, s, p);
+  } else {
+    hipLaunchKernelGGL((k_route_pool<float, false>), gpool, dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_route_proj<float>, gproj, dim3(256), shm, s, p);
+  }
+}
+
+// The one-kernel forms (bf16 MLP2, Hr = 128, many tokens).
 hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s) {
   const size_t ntok = static_cast<size_t>(p.B) * p.T;
   if (ntok == 0) return hipSuccess;
-  const bool mfma_ok = bf16 && p.kind == 0 && p.Hr == 128 && p.C >= 1 && p.C <= 16 &&
-                       p.G <= 32 && p.d % kRtKc == 0 && ntok < (1u << 30);
-  const int vec = bf16 ? 8 : 4;
+  constexpr int vec = 8;
   const int ncb = (p.d + 64 * vec - 1) / (64 * vec);
-  const bool pcb_ok = bf16 && p.kind == 0 && p.pcb && p.d % (64 * vec) == 0 && p.d_e % 8 == 0 &&
-                      p.Hr % 64 == 0 && p.Hr <= 128 && p.C >= 1 &&
+  const bool pcb_ok = p.pcb && p.d_e % 8 == 0 &&
                       static_cast<size_t>(p.Hr) * (2 * static_cast<size_t>(p.d) + p.d_e) * 2 < (1ull << 31) &&
                       static_cast<size_t>(ncb) * p.B * p.Hr * 4 < (1ull << 31) &&
                       ((reinterpret_cast<uintptr_t>(p.W1) | reinterpret_cast<uintptr_t>(p.E)) & 15) == 0;
   // the MFMA router adds the partial language terms itself when a block of
   // its tokens spans at most two samples and there are at most 8 partials
-  const bool ps = mfma_ok && pcb_ok && p.T >= kRtTok && ncb <= 8;
-  {
-    const dim3 gpool(static_cast<unsigned>(p.B * ncb));
-    const int nout = p.kind == 0 ? p.Hr : p.G;
-    const int nF = ((p.kind == 0 ? p.Hr : p.G) + 3) / 4;
-    const dim3 gproj(static_cast<unsigned>(p.B * ((nout + 7) / 8) + nF));
-    const size_t shm = static_cast<size_t>(p.d) * sizeof(float);
-    if (pcb_ok) {
-      const unsigned nfb = static_cast<unsigned>((p.Hr * p.C + 255) / 256);
-      hipLaunchKernelGGL((k_route_pool<rolesub::bf16, true>), dim3(gpool.x + nfb), dim3(256), 0, s, p);
-      if (!ps)
-        hipLaunchKernelGGL(k_route_cbsum, dim3(static_cast<unsigned>((p.B * p.Hr + 255) / 256)), dim3(256), 0,
-                           s, p, ncb);
-    } else if (bf16) {
-      hipLaunchKernelGGL((k_route_pool<rolesub::bf16, false>), gpool, dim3(256), 0, s, p);
-      hipLaunchKernelGGL(k_route_proj<rolesub::bf16>, gproj, dim3(256), shm, s, p);
-    } else {
-      hipLaunchKernelGGL((k_route_pool<float, false>), gpool, dim3(256), 0, s, p);
-      hipLaunchKernelGGL(k_route_proj<float>, gproj, dim3(256), shm, s, p);
-    }
+  const bool ps = pcb_ok && p.T >= kRtTok && ncb <= 8;
+  if (pcb_ok) {
+    const unsigned nfb = static_cast<unsigned>((p.Hr * p.C + 255) / 256);
+    if (p.d % (64 * vec) == 0)
+      hipLaunchKernelGGL((k_route_pool<rolesub::bf16, true>), dim3(static_cast<unsigned>(p.B * ncb) + nfb), dim3(256), 0,
+                         s, p);
+    else
+      launch_pool_any(p, s);
+    if (!ps)
+      hipLaunchKernelGGL(k_route_cbsum, dim3(static_cast<unsigned>((p.B * p.Hr + 255) / 256)), dim3(256), 0,
+                         s, p, ncb);
+  } else {
+    launch_pool_proj(p, true, s);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (mfma_ok && ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0) {
+  if (ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0) {
     const dim3 grid(static_cast<unsigned>(2 * route_sk_tiles(p.B, p.T)));
     if (p.G <= 8) hipLaunchKernelGGL(k_route_mlp2_sk<8>, grid, dim3(64 * kSkW), 0, s, p, ncb);
     else if (p.G <= 16) hipLaunchKernelGGL(k_route_mlp2_sk<16>, grid, dim3(64 * kSkW), 0, s, p, ncb);
     else hipLaunchKernelGGL(k_route_mlp2_sk<32>, grid, dim3(64 * kSkW), 0, s, p, ncb);
-  } else if (mfma_ok) {
+  } else {
     const dim3 grid(static_cast<unsigned>((ntok + kRtTok - 1) / kRtTok));
     if (ps) {
       if (p.G <= 8) hipLaunchKernelGGL((k_route_mlp2_bf16<8, true>), grid, dim3(256), 0, s, p, ncb);
@@ -1322,21 +1260,8 @@ hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s) {
       else if (p.G <= 16) hipLaunchKernelGGL((k_route_mlp2_bf16<16, false>), grid, dim3(256), 0, s, p, 0);
       else hipLaunchKernelGGL((k_route_mlp2_bf16<32, false>), grid, dim3(256), 0, s, p, 0);
     }
-  } else {
-    const int nmain = p.kind == 0 ? p.Hr : p.G;
-    const size_t shm = sizeof(float) * (static_cast<size_t>(p.d) + nmain + p.C +
-                                        (p.kind == 0 ? p.Hr : 0) + p.G);
-    if (bf16)
-      hipLaunchKernelGGL(k_route_generic<rolesub::bf16>, dim3(static_cast<unsigned>(ntok)), dim3(256), shm, s, p);
-    else
-      hipLaunchKernelGGL(k_route_generic<float>, dim3(static_cast<unsigned>(ntok)), dim3(256), shm, s, p);
   }
   return hipGetLastError();
-}
-
-size_t route_generic_shm(int d, int G, int C, int Hr, int kind) {
-  const int nmain = kind == 0 ? Hr : G;
-  return sizeof(float) * (static_cast<size_t>(d) + nmain + C + (kind == 0 ? Hr : 0) + G);
 }
 
 hipError_t launch_select(const RouteParams& p, hipStream_t s) {

@@ -18,6 +18,8 @@ struct RouteParams {
   float* pcb;   // [ncb][B][Hr] partial language terms per column block (bf16 MLP2; workspace)
   float* rpart;  // split-K router: both halves' partial products per 96-token tile, or null (workspace)
   int* rcnt;     // split-K router: finished halves per tile, zeroed by the pool kernel (workspace)
+  float* part;      // two-kernel form: partial products (workspace) and their bytes
+  size_t part_bytes;
   int sk_polls;  // split-K router: polls the first half of a tile makes for the second (0: never shares)
   int mode;
   int k_by_type[4];
@@ -32,9 +34,11 @@ struct RouteParams {
   uint8_t* count;
 };
 
+// Row stride (floats) of the per-sample language terms: whole 16-byte pieces.
+__host__ __device__ inline size_t route_ld(int n) { return n < 1 ? 0 : (static_cast<size_t>(n) + 3) & ~size_t{3}; }
 // Sizes of the route workspace pieces (floats).
 inline size_t route_cb_floats(int B, int Hr, int G, int kind) {
-  return static_cast<size_t>(B) * (kind == 0 ? Hr : G);
+  return static_cast<size_t>(B) * route_ld(kind == 0 ? Hr : G);
 }
 inline size_t route_F_floats(int Hr, int G, int C, int kind) {
   return static_cast<size_t>(kind == 0 ? Hr : G) * C;
@@ -42,8 +46,8 @@ inline size_t route_F_floats(int Hr, int G, int C, int kind) {
 inline size_t route_hbar_floats(int B, int d) { return static_cast<size_t>(B) * d; }
 // column blocks of 256 (the smallest block the pool kernel uses, f32) bound
 // the number of partial language terms for any dtype
-inline size_t route_pcb_floats(int B, int d, int Hr, int kind) {
-  return kind == 0 ? static_cast<size_t>((d + 255) / 256) * B * Hr : 0;
+inline size_t route_pcb_floats(int B, int d, int Hr, int G, int kind) {
+  return static_cast<size_t>((d + 255) / 256) * B * route_ld(kind == 0 ? Hr : G);
 }
 
 // Split-K form of the bf16 MLP2 router (Hr = 128): 96-token tiles, each
@@ -60,9 +64,57 @@ inline size_t route_sk_cnt_ints(int B, int T, int Hr, int kind) {
   return kind == 0 && Hr == 128 ? route_sk_tiles(B, T) : 0;
 }
 
+// Two-kernel form (k_route_tile.hip): 64-token tiles x row blocks x slices of
+// the hidden size. MB: 16-row blocks of the router's matrices in all.
+inline int route_tile_blocks(int Hr, int G, int C, int kind) {
+  auto blocks = [](int n) { return n < 1 ? 0 : (n - 1) / 16 + 1; };
+  const int MB = blocks(kind == 0 ? Hr : G) + blocks(C);
+  return MB < 1 ? 1 : MB;  // sizes are asked for before the router is checked
+}
+inline int route_tile_rows(int MB) { return MB <= 2 ? 2 : 3; }  // row blocks per workgroup
+// Slices of the hidden size: the same for every batch, so that a token's sums
+// do not depend on which others share the call. bf16 MLP2: the two halves the
+// one-kernel forms sum. Otherwise what fills the chip over the range of batches
+// (additive, at most five row blocks: 4; f32, whose stages take four times the
+// matrix-core time: 8), with the partial products of a tile within 2 MiB and a
+// stage at least in every slice.
+inline int route_tile_smax(int MB, int want) {
+  const size_t n = (size_t{2} << 20) / (static_cast<size_t>(MB) * 4096);
+  return n < 1 ? 1 : n > static_cast<size_t>(want) ? want : static_cast<int>(n);
+}
+constexpr int kRouteSlicesBf16 = 4, kRouteSlicesF32 = 8;  // at most
+inline int route_tile_slices(int d, int MB, int kind, bool bf16) {
+  const int nch = static_cast<int>((static_cast<size_t>(d) * (bf16 ? 2 : 4) + 127) / 128);
+  const int s = route_tile_smax(MB, !bf16 ? kRouteSlicesF32 : kind == 0 ? 2 : kRouteSlicesBf16);
+  return s < nch ? s : nch;
+}
+constexpr size_t kRouteTileArea = size_t{16} << 20;
+// Operands of the finishing kernel in its own layout: F as matrix-core
+// fragments of whole 16 x 16 blocks, W2 in the lanes' order, padded biases.
+inline size_t route_fold_floats(int Hr, int G, int C, int kind) {
+  const size_t nb = route_tile_blocks(Hr, G, 0, kind), rb = route_tile_blocks(C, C, 0, 0);
+  return nb * rb * 256 + (kind == 0 ? nb * G * 16 : 0) + rb * 16 + nb * 16;
+}
+// bytes of folded operands and partial products: an upper bound that never falls as B or T grows
+// (a workspace sized for a batch serves every smaller one); calls with more
+// tokens run in several launches
+inline size_t route_tile_bytes(int B, int T, int Hr, int G, int C, int kind) {
+  const int MB = route_tile_blocks(Hr, G, C, kind);
+  const size_t tiles = (static_cast<size_t>(B) * T + 63) / 64;
+  const size_t bytes = tiles * route_tile_smax(MB, kRouteSlicesF32) * MB * 4096;
+  return (bytes < kRouteTileArea ? bytes : kRouteTileArea) + route_fold_floats(Hr, G, C, kind) * sizeof(float);
+}
+hipError_t launch_route_tile(const RouteParams& p, bool bf16, size_t part_bytes, hipStream_t s);
+// Shares of the language terms (p.pcb), folded role terms (p.F) and cleared
+// tile counters for the one-kernel forms, any hidden size of 16-byte rows.
+void launch_pool_any(const RouteParams& p, hipStream_t s);
+// Pooled language states, language terms (p.cb) and folded role terms (p.F)
+// for any strides and alignment.
+void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s);
+
+// Whether a call runs in the two-kernel form (a function of shape and type only).
+bool route_uses_tiles(int B, int T, int d, int G, int C, int Hr, int kind, bool bf16);
 hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s);
-// LDS bytes the generic (one token per workgroup) router needs.
-size_t route_generic_shm(int d, int G, int C, int Hr, int kind);
 hipError_t launch_select(const RouteParams& p, hipStream_t s);
 
 // Role-driven within-type group allocation (and optional selection).

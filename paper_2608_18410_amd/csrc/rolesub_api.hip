@@ -109,18 +109,39 @@ rolesub_status check_capacity(const rolesub_dims* dims, const rolesub_budget* bu
   return ROLESUB_OK;
 }
 
-// Route workspace: cb, F, hbar and the partial language terms, then (with
-// split) the partial products and tile counters of the split-K router.
-size_t route_ws_bytes(const rolesub_dims* d, const rolesub_router* r, bool split = true) {
+// Route workspace: cb, F, hbar and the partial language terms, then one area
+// for the partial products: those and the tile counters of the split-K router,
+// or those of the two-kernel form.
+struct RouteWs {
+  size_t off_F, off_h, off_p, off_s, off_c, end;
+};
+
+RouteWs route_ws(int B, int T, int d, int G, int C, int Hr, int kind) {
+  RouteWs w;
+  w.off_F = align256(route_cb_floats(B, Hr, G, kind) * sizeof(float));
+  w.off_h = w.off_F + align256(route_F_floats(Hr, G, C, kind) * sizeof(float));
+  w.off_p = w.off_h + align256(route_hbar_floats(B, d) * sizeof(float));
+  w.off_s = w.off_p + align256(route_pcb_floats(B, d, Hr, G, kind) * sizeof(float));
+  w.off_c = w.off_s + align256(route_sk_part_floats(B, T, Hr, kind) * sizeof(float));
+  w.end = std::max(w.off_c + align256(route_sk_cnt_ints(B, T, Hr, kind) * sizeof(int)),
+                   w.off_s + align256(route_tile_bytes(B, T, Hr, G, C, kind)));
+  return w;
+}
+
+size_t route_ws_bytes(const rolesub_dims* d, const rolesub_router* r) {
   if (!d || !r || d->B <= 0) return 0;
-  const int T = d->T > 0 ? d->T : 0;
-  return align256(route_cb_floats(d->B, r->Hr, d->G, r->kind) * sizeof(float)) +
-         align256(route_F_floats(r->Hr, d->G, r->C, r->kind) * sizeof(float)) +
-         align256(route_hbar_floats(d->B, d->d > 0 ? d->d : 0) * sizeof(float)) +
-         align256(route_pcb_floats(d->B, d->d > 0 ? d->d : 0, r->Hr, r->kind) * sizeof(float)) +
-         (split ? align256(route_sk_part_floats(d->B, T, r->Hr, r->kind) * sizeof(float)) +
-                      align256(route_sk_cnt_ints(d->B, T, r->Hr, r->kind) * sizeof(int))
-                : 0);
+  return route_ws(d->B, d->T > 0 ? d->T : 0, d->d > 0 ? d->d : 0, d->G, r->C, r->Hr, r->kind).end;
+}
+
+// What rolesub_route_noalloc counts against its array: the workspace without
+// the areas of partial products (and partial language terms of the additive
+// router), which it sizes by the room left.
+size_t noalloc_bytes(const rolesub_dims* d, const rolesub_router* r) {
+  const int B = d->B, dd = d->d > 0 ? d->d : 0;
+  const size_t n = r->kind == 0 ? r->Hr : d->G;
+  return align256(B * n * sizeof(float)) + align256(route_F_floats(r->Hr, d->G, r->C, r->kind) * sizeof(float)) +
+         align256(route_hbar_floats(B, dd) * sizeof(float)) +
+         (r->kind == 0 ? align256((static_cast<size_t>(dd) + 255) / 256 * B * n * sizeof(float)) : 0);
 }
 
 // Polls the first half of a split-K router tile makes for the second before
@@ -135,10 +156,9 @@ int route_sk_polls() {
 }
 
 // Checks the router and hidden states and fills the router part of p (B, T,
-// d, G already set); the route workspace sits at the start of `workspace`.
+// d, G already set).
 rolesub_status setup_router(const char* fn, const rolesub_dims* dims, rolesub_dtype dtype,
-                            const rolesub_router* router, const void* h, void* workspace, size_t ws_bytes,
-                            RouteParams& p, bool split = true) {
+                            const rolesub_router* router, const void* h, RouteParams& p) {
   if (!h) return fail(ROLESUB_ERR_INVALID_ARG, "%s: h must be non-NULL", fn);
   if (dims->d < 1) return fail(ROLESUB_ERR_INVALID_ARG, "%s: hidden size d=%d", fn, dims->d);
   if (router->C < 1 || router->C > 64)
@@ -157,16 +177,13 @@ rolesub_status setup_router(const char* fn, const rolesub_dims* dims, rolesub_dt
   } else {
     return fail(ROLESUB_ERR_INVALID_ARG, "%s: unknown router kind %d", fn, router->kind);
   }
-  if (route_generic_shm(dims->d, dims->G, router->C, router->Hr, router->kind) > 64 * 1024 ||
-      static_cast<size_t>(dims->d) * sizeof(float) > 64 * 1024)
+  // the hidden state, the products and the hidden units of one token, as floats
+  const size_t nmain = router->kind == ROLESUB_ROUTER_MLP2 ? 2 * static_cast<size_t>(router->Hr) : dims->G;
+  if ((static_cast<size_t>(dims->d) + nmain + router->C + dims->G) * sizeof(float) > 64 * 1024)
     return fail(ROLESUB_ERR_UNSUPPORTED, "%s: hidden size d=%d too large", fn, dims->d);
   if (static_cast<size_t>(dims->T) * dims->d * esize(dtype) >= kMaxRegion ||
       static_cast<size_t>(router->Hr) * (2 * static_cast<size_t>(dims->d) + router->d_e) * esize(dtype) >= kMaxRegion)
     return fail(ROLESUB_ERR_UNSUPPORTED, "%s: one sample's hidden states exceed 2 GiB", fn);
-  const size_t need = route_ws_bytes(dims, router, split);
-  if (ws_bytes < need || (need && !workspace))
-    return fail(ROLESUB_ERR_INVALID_ARG, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws_bytes);
-
   p.d_e = router->d_e;
   p.Hr = router->Hr;
   p.C = router->C;
@@ -186,24 +203,63 @@ rolesub_status setup_router(const char* fn, const rolesub_dims* dims, rolesub_dt
   p.W_role = router->W_role;
   p.W_lang = router->W_lang;
   p.b_lang = router->b_lang;
+  return ROLESUB_OK;
+}
+
+// The two-kernel form of p's call in a workspace of `bytes` (its layout, with
+// the area of partial products ending at `bytes`).
+hipError_t run_tiles(RouteParams p, bool bf16, void* workspace, size_t bytes, hipStream_t s) {
+  const RouteWs w = route_ws(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind);
   char* ws = static_cast<char*>(workspace);
   p.cb = reinterpret_cast<float*>(ws);
-  const size_t off_F = align256(route_cb_floats(p.B, p.Hr, p.G, p.kind) * sizeof(float));
-  const size_t off_h = off_F + align256(route_F_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float));
-  const size_t off_p = off_h + align256(route_hbar_floats(p.B, p.d) * sizeof(float));
-  p.F = reinterpret_cast<float*>(ws + off_F);
-  p.hbar = reinterpret_cast<float*>(ws + off_h);
-  p.pcb = reinterpret_cast<float*>(ws + off_p);
+  p.F = reinterpret_cast<float*>(ws + w.off_F);
+  p.hbar = reinterpret_cast<float*>(ws + w.off_h);
+  p.pcb = reinterpret_cast<float*>(ws + w.off_p);
   p.rpart = nullptr;
   p.rcnt = nullptr;
-  if (split && route_sk_cnt_ints(p.B, p.T, p.Hr, p.kind)) {
-    const size_t off_s = off_p + align256(route_pcb_floats(p.B, p.d, p.Hr, p.kind) * sizeof(float));
-    const size_t off_c = off_s + align256(route_sk_part_floats(p.B, p.T, p.Hr, p.kind) * sizeof(float));
-    p.rpart = reinterpret_cast<float*>(ws + off_s);
-    p.rcnt = reinterpret_cast<int*>(ws + off_c);
+  p.part = reinterpret_cast<float*>(ws + w.off_s);
+  return launch_route_tile(p, bf16, bytes - w.off_s, s);
+}
+
+// Router and selection of p's call in `workspace`. split: it holds
+// route_ws_bytes(); otherwise it is the no-alloc call's array, whose acceptance
+// has been checked: the single-kernel router needs no area of partial products,
+// and the two-kernel form runs over ranges of samples that leave room for one.
+hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes, bool split, hipStream_t s) {
+  const RouteWs w = route_ws(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind);
+  if (!route_uses_tiles(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind, bf16)) {
+    char* ws = static_cast<char*>(workspace);
+    p.cb = reinterpret_cast<float*>(ws);
+    p.F = reinterpret_cast<float*>(ws + w.off_F);
+    p.hbar = reinterpret_cast<float*>(ws + w.off_h);
+    p.pcb = reinterpret_cast<float*>(ws + w.off_p);
+    p.rpart = split ? reinterpret_cast<float*>(ws + w.off_s) : nullptr;
+    p.rcnt = split ? reinterpret_cast<int*>(ws + w.off_c) : nullptr;
     p.sk_polls = route_sk_polls();
+    return launch_route(p, bf16, s);
   }
-  return ROLESUB_OK;
+  if (split) return run_tiles(p, bf16, workspace, w.end, s);
+  // room for the folded operands and the partial products of one tile at least
+  // (2.2 MiB hold those of any router, see route_tile_smax; with one sample
+  // everything takes less than 7.5 MiB, since d + 2 Hr <= 16384)
+  const size_t room = route_fold_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float) + (size_t{9} << 18);
+  int nb = p.B;
+  while (nb > 1 && route_ws(nb, p.T, p.d, p.G, p.C, p.Hr, p.kind).off_s + room > ws_bytes) nb = (nb + 1) / 2;
+  const size_t es = bf16 ? 2 : 4, T = static_cast<size_t>(p.T);
+  for (int b0 = 0; b0 < p.B; b0 += nb) {
+    RouteParams q = p;
+    const size_t t0 = b0 * T;
+    q.B = std::min(nb, p.B - b0);
+    q.h = static_cast<const char*>(p.h) + t0 * p.d * es;
+    q.types = p.types + t0;
+    if (p.scores_out) q.scores_out = p.scores_out + t0 * p.G;
+    if (p.mask) q.mask = p.mask + t0;
+    if (p.idx) q.idx = p.idx + t0 * p.G;
+    if (p.count) q.count = p.count + t0;
+    const hipError_t e = run_tiles(q, bf16, workspace, ws_bytes, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Device address of the current device's copy of `scratch`, looked up once
@@ -360,20 +416,23 @@ rolesub_status route_impl(const char* fn, const rolesub_dims* dims, rolesub_dtyp
   if (scores_in) return from_hip(launch_select(p, s), fn);
 
   if (!router) return fail(ROLESUB_ERR_INVALID_ARG, "%s: router is NULL and no scores_in given", fn);
-  // the no-alloc call runs the single-kernel router (its array holds no
-  // split-K partials); both forms give bitwise-equal results
+  st = setup_router(fn, dims, dtype, router, h, p);
+  if (st) return st;
+  // the no-alloc call runs the single-kernel router where the other runs its
+  // split-K form (its array holds no split-K partials); both give
+  // bitwise-equal results
+  const size_t need = use_scratch ? noalloc_bytes(dims, router) : route_ws_bytes(dims, router);
   if (use_scratch) {
-    const size_t need = route_ws_bytes(dims, router, false);
     if (need > ROLESUB_ROUTE_NOALLOC_MAX_BYTES)
       return fail(ROLESUB_ERR_UNSUPPORTED, "%s: needs %zu bytes of route workspace, above the %zu bytes it holds", fn,
                   need, static_cast<size_t>(ROLESUB_ROUTE_NOALLOC_MAX_BYTES));
     st = scratch_on_current_device(fn, s, &workspace);
     if (st) return st;
     ws_bytes = ROLESUB_ROUTE_NOALLOC_MAX_BYTES;
+  } else if (ws_bytes < need || !workspace) {
+    return fail(ROLESUB_ERR_INVALID_ARG, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws_bytes);
   }
-  st = setup_router(fn, dims, dtype, router, h, workspace, ws_bytes, p, !use_scratch);
-  if (st) return st;
-  return from_hip(launch_route(p, dtype == ROLESUB_BF16, s), fn);
+  return from_hip(run_route(p, dtype == ROLESUB_BF16, workspace, ws_bytes, !use_scratch, s), fn);
 }
 
 }  // namespace
@@ -487,7 +546,7 @@ rolesub_status rolesub_route_allocate(const rolesub_dims* dims, rolesub_dtype dt
   p.d = dims->d;
   p.G = dims->G;
   p.types = token_type;
-  st = setup_router(fn, dims, dtype, router, h, workspace, ws_bytes, p);
+  st = setup_router(fn, dims, dtype, router, h, p);
   if (st) return st;
   // scores and priorities go to the caller's buffers or to the workspace tail
   char* tail = static_cast<char*>(workspace) + route_ws_bytes(dims, router);
@@ -500,7 +559,7 @@ rolesub_status rolesub_route_allocate(const rolesub_dims* dims, rolesub_dtype dt
   p.priority = pr;
   p.mask = nullptr;  // the selection waits for the allocation
   hipStream_t s = static_cast<hipStream_t>(stream);
-  st = from_hip(launch_route(p, dtype == ROLESUB_BF16, s), fn);
+  st = from_hip(run_route(p, dtype == ROLESUB_BF16, workspace, route_ws_bytes(dims, router), true, s), fn);
   if (st) return st;
   AllocParams a = alloc_params(dims->B, dims->T, dims->G, k_by_type);
   a.priority = pr;
