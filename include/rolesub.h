@@ -32,8 +32,6 @@
  *     Inside kernels accumulation and softmax are f32; bf16 outputs are
  *     rounded to nearest even.
  *   - Supported shapes: dh in {64, 128}; G divides dh; 1 <= G <= 32.
- *     The bf16 path uses matrix-core kernels for dh = 128 and vector kernels
- *     otherwise.
  *
  * Routing space reading: every head h has its own orthonormal R_h (dh x dh);
  * group s of a token is the s-th slice of width ds = dh/G of each head's

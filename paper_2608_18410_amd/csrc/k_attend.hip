@@ -500,66 +500,214 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ---------------------------------------------------------------------------
-// Vector-ALU kernel for f32 (and any head width). One workgroup per
-// (sample, head, query); thread j owns output dimension j.
-template <class E>
-__global__ __launch_bounds__(128) void k_attend_generic(AttendParams p) {
-  __shared__ float red[2];
-  __shared__ float us[128];
-  const int dh = p.dh, j = threadIdx.x, lane = j & 63, w = j >> 6;
-  const size_t id = blockIdx.x;
-  const int qi = static_cast<int>(id % p.Tq);
-  const int h = static_cast<int>((id / p.Tq) % p.H);
-  const int b = static_cast<int>(id / (static_cast<size_t>(p.Tq) * p.H));
-  const int T = p.T, H = p.H, G = p.G, ds = dh / G;
-  const int g = j / ds, e = j % ds;
+// f32 matrix-core kernel (16x16x4). One workgroup = one (sample, head) and 16
+// queries; its four waves take the 16-token tiles w, w + 4, ... , each with its
+// own running softmax, and the four (maximum, sum, U) are merged at the end, so
+// that a short prefix still occupies four waves and no barrier stands in the
+// key loop. Operands go from memory straight into the registers that the MFMAs
+// read:
+//   S^T = K Q^T   a 16-byte load per lane (token l16, dims 16kk + 4 g4 ..) is the
+//                 A operand of four MFMAs whose k = g4 is dim 16kk + 4 g4 + i;
+//                 the queries, loaded the same way, are B;
+//   U^T += Z~^T P^T   k = g4 is token 4 g4 + i, whose probability the lane holds;
+//                 A is one value per lane, dim 16m + l16 of that token, read
+//                 from its slot of the packed cache (dropped groups load zero);
+//   O^T = R_h U^T  output rows split over the waves, U from LDS in its own layout.
+// Bound by the f32 matrix rate (32 cycles per 16x16x4) and, with few prefixes,
+// by each wave's chain of tiles. Measured (2 prefixes of 177 tokens, 56 queries,
+// 32 heads of 128): 15.8 us against 196 of a vector-ALU kernel with one
+// workgroup per query; 80 tokens, 8 queries, 4 heads of 64: 6.6 against 57.
+template <int DH>
+__global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
+  constexpr int MT = DH / 16;  // 16-dim blocks
+  __shared__ __attribute__((aligned(16))) f32x4 s_u[4][MT][64];
+  __shared__ float s_m[4][16], s_l[4][16];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = p.T, H = p.H, G = p.G, ds = DH / G, lds = __builtin_ctz(ds);  // G divides DH, a power of two
   const uint32_t gm = group_mask(G);
-  const E* qv = static_cast<const E*>(p.q) + ((static_cast<size_t>(b) * p.Tq + qi) * H + h) * dh;
-  const E* kv = static_cast<const E*>(p.k);
-  const E* Vp = static_cast<const E*>(p.Vp);
-  const float qj = tof(qv[j]);
-  float m = -INFINITY, l = 0.f, u = 0.f;
-  const int nw = (dh + 63) / 64;
-  const int t_stop = p.causal ? min(T, qi + 1) : T;
-  for (int t = 0; t < t_stop; ++t) {
-    float part = qj * tof(kv[((static_cast<size_t>(b) * T + t) * H + h) * dh + j]);
-    part = wave_sum(part);
-    if (nw > 1) {
-      if (lane == 0) red[w] = part;
-      __syncthreads();
-      part = red[0] + red[1];
-      __syncthreads();
-    }
-    const float sc = part * p.scale;
-    const float mn = fmaxf(m, sc);
-    const float al = expf(m - mn), pr = expf(sc - mn);
-    l = l * al + pr;
-    const uint32_t mk = p.mask[static_cast<size_t>(b) * T + t] & gm;
-    float zv = 0.f;
-    if ((mk >> g) & 1u) {
-      const int64_t slot = p.offsets[static_cast<size_t>(b) * (T + 1) + t] + __popc(mk & ((1u << g) - 1u));
-      if (slot < p.cap) zv = tof(Vp[((static_cast<size_t>(b) * H + h) * p.cap + slot) * ds + e]);
-    }
-    u = u * al + pr * zv;
-    m = mn;
+  // the query blocks of one (sample, head) are consecutive on one XCD where
+  // possible: the later ones read its keys and values from that L2
+  const int nqb = (p.Tq + 15) / 16, lin = blockIdx.x;
+  int item, qb, h, b;
+  if ((p.B * H) % 8 == 0) {
+    const int xcd = lin & 7, slot = lin >> 3;
+    item = (slot / nqb) * 8 + xcd;
+    qb = slot % nqb;
+  } else {
+    item = lin / nqb;
+    qb = lin % nqb;
   }
-  us[j] = u / l;
+  xcd_split(item, H, h, b);
+  const int qq = qb * 16 + l16;  // this lane's query
+  const float sl2 = p.scale * 1.4426950408889634f;
+
+  const uint32_t stride = static_cast<uint32_t>(H) * DH * 4;  // bytes between tokens
+  const rsrc_t r_q = make_rsrc(static_cast<const float*>(p.q) + (static_cast<size_t>(b) * p.Tq * H + h) * DH,
+                               clamp_bytes(static_cast<size_t>(p.Tq - 1) * stride + DH * 4));
+  const rsrc_t r_k = make_rsrc(static_cast<const float*>(p.k) + (static_cast<size_t>(b) * T * H + h) * DH,
+                               clamp_bytes(static_cast<size_t>(T - 1) * stride + DH * 4));
+  const rsrc_t r_mask = make_rsrc(p.mask + static_cast<size_t>(b) * T, T * 4u);
+  const rsrc_t r_off = make_rsrc(p.offsets + static_cast<size_t>(b) * (T + 1), (T + 1) * 4u);
+  const rsrc_t r_v = make_rsrc(static_cast<const float*>(p.Vp) + (static_cast<size_t>(b) * H + h) * p.cap * ds,
+                               clamp_bytes(static_cast<size_t>(p.cap) * ds * 4));
+  const int cap32 = static_cast<int>(p.cap);  // < 2^31: the cache per (sample, head) is < 2 GiB
+
+  u32x4 qf[MT];
+#pragma unroll
+  for (int kk = 0; kk < MT; ++kk)
+    qf[kk] = bload16(r_q, oob_unless(qq < p.Tq, static_cast<uint32_t>(qq) * stride + 64u * kk + 16u * g4));
+
+  struct Meta {
+    uint32_t m[4];
+    int32_t o[4];
+  };
+  struct Tile {
+    u32x4 k[MT];
+    float v[4][MT];
+  };
+  auto load_meta = [&](Meta& x, int t0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + 4 * g4 + i;
+      x.m[i] = bload4(r_mask, oob_unless(t < T, 4u * t));
+      x.o[i] = static_cast<int32_t>(bload4(r_off, oob_unless(t < T, 4u * t)));
+    }
+  };
+  auto load_tile = [&](Tile& x, const Meta& mt, int t0) {
+#pragma unroll
+    for (int kk = 0; kk < MT; ++kk)
+      x.k[kk] = bload16(r_k, oob_unless(t0 + l16 < T, static_cast<uint32_t>(t0 + l16) * stride + 64u * kk + 16u * g4));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t m = mt.m[i] & gm;  // zero past T
+#pragma unroll
+      for (int mm = 0; mm < MT; ++mm) {
+        const int dim = 16 * mm + l16, g = dim >> lds;
+        const int sl = mt.o[i] + __popc(m & ((1u << g) - 1u));
+        const bool ok = (((m >> g) & 1u) != 0u) & (sl < cap32);
+        x.v[i][mm] = __uint_as_float(bload4(r_v, oob_unless(ok, static_cast<uint32_t>(sl * ds + (dim & (ds - 1))) * 4u)));
+      }
+    }
+  };
+
+  f32x4 acc[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+  auto compute = [&](const Tile& x, int t0) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: a single one waits for each MFMA's result
+#pragma unroll
+    for (int kk = 0; kk < MT; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4& s = (i & 1) ? s1 : s0;
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x.k[kk][i]), __uint_as_float(qf[kk][i]), s, 0, 0, 0);
+      }
+    float v[4], mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + 4 * g4 + i;
+      v[i] = (t < T) & (!p.causal | (t <= qq)) ? (s0[i] + s1[i]) * sl2 : -INFINITY;
+      mx = fmaxf(mx, v[i]);
+    }
+    mx = max_xor32(max_xor16(mx));
+    if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[m] *= alpha;
+      l_run *= alpha;
+      m_run = m_new;
+    }
+    const float ref = m_run == -INFINITY ? 0.f : m_run;  // every key so far masked for this query
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = __builtin_amdgcn_exp2f(v[i] - ref);
+      l_run += v[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[i][m], v[i], acc[m], 0, 0, 0);
+  };
+
+  // tiles w, w + 4, ...: keys and values one tile ahead, the masks and offsets
+  // that address the values two
+  const int t_stop = p.causal ? min(T, qb * 16 + 16) : T;
+  Meta mA, mB;
+  Tile A, B;
+  int t0 = 16 * w;
+  load_meta(mA, t0);
+  load_meta(mB, t0 + 64);
+  load_tile(A, mA, t0);
+  while (t0 < t_stop) {
+    load_meta(mA, t0 + 128);
+    load_tile(B, mB, t0 + 64);
+    compute(A, t0);
+    t0 += 64;
+    if (t0 >= t_stop) break;
+    load_meta(mB, t0 + 128);
+    load_tile(A, mA, t0 + 64);
+    compute(B, t0);
+    t0 += 64;
+  }
+
+  // ---- merge the four waves' softmax states and U
+  l_run = add_xor32(add_xor16(l_run));
+#pragma unroll
+  for (int m = 0; m < MT; ++m) s_u[w][m][lane] = acc[m];
+  if (g4 == 0) {
+    s_m[w][l16] = m_run;
+    s_l[w][l16] = l_run;
+  }
   __syncthreads();
-  const E* Rh = static_cast<const E*>(p.R) + static_cast<size_t>(h) * dh * dh;
-  float o = 0.f;
-  for (int jj = 0; jj < dh; ++jj) o += tof(Rh[j * dh + jj]) * us[jj];
-  const size_t oi = ((static_cast<size_t>(b) * p.Tq + qi) * H + h) * dh + j;
-  if (p.out_f32)
-    static_cast<float*>(p.out)[oi] = o;
-  else
-    static_cast<E*>(p.out)[oi] = fromf<E>(o);
+  const float ma = fmaxf(fmaxf(s_m[0][l16], s_m[1][l16]), fmaxf(s_m[2][l16], s_m[3][l16]));
+  float f[4], l = 0.f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float mv = s_m[v][l16];
+    f[v] = mv == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mv - ma);  // no key seen: no share
+    l += s_l[v][l16] * f[v];
+  }
+  const float inv = 1.f / l;
+  f32x4 u[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    u[m] = s_u[0][m][lane] * f[0];
+#pragma unroll
+    for (int v = 1; v < 4; ++v) u[m] += s_u[v][m][lane] * f[v];
+    u[m] *= inv;
+  }
+  // ---- O^T = R_h U^T: wave w gives output blocks w, w + 4, ..
+  const rsrc_t r_R = make_rsrc(static_cast<const float*>(p.R) + static_cast<size_t>(h) * DH * DH, DH * DH * 4);
+  const rsrc_t r_o = make_rsrc(static_cast<float*>(p.out) + (static_cast<size_t>(b) * p.Tq * H + h) * DH,
+                               clamp_bytes(static_cast<size_t>(p.Tq - 1) * stride + DH * 4));
+#pragma unroll
+  for (int e = 0; e < MT / 4; ++e) {
+    const int m = w + 4 * e;
+    u32x4 rr[MT];
+#pragma unroll
+    for (int kk = 0; kk < MT; ++kk) rr[kk] = bload16(r_R, 4u * ((16 * m + l16) * DH + 16 * kk + 4 * g4));
+    f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+#pragma unroll
+    for (int kk = 0; kk < MT; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4& o = (i & 1) ? o1 : o0;
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(rr[kk][i]), u[kk][i], o, 0, 0, 0);
+      }
+    o0 += o1;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o0), r_o,
+                                           oob_unless(qq < p.Tq, static_cast<uint32_t>(qq) * stride + 64u * m + 16u * g4), 0, 0);
+  }
 }
 
 }  // namespace
 
 hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
   if (p.B == 0 || p.Tq == 0 || p.H == 0) return hipSuccess;
-  if (bf16 && (p.dh == 128 || p.dh == 64)) {
+  if (bf16) {
     const dim3 grid(static_cast<unsigned>(p.B * p.H * ((p.Tq + 63) / 64)));
     const int ds = p.dh / p.G;
     const int vm = ds >= 8 ? kWide : (ds == 4 ? kDs4 : kDs2);
@@ -570,11 +718,9 @@ hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
                                                                                  : k_attend_bf16<64, kDs2>);
     hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   } else {
-    const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * p.Tq));
-    if (bf16)
-      hipLaunchKernelGGL(k_attend_generic<rolesub::bf16>, grid, dim3(p.dh), 0, s, p);
-    else
-      hipLaunchKernelGGL(k_attend_generic<float>, grid, dim3(p.dh), 0, s, p);
+    const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * ((p.Tq + 15) / 16)));
+    if (p.dh == 128) hipLaunchKernelGGL(k_attend_f32<128>, grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(k_attend_f32<64>, grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }

@@ -1,4 +1,6 @@
 // Value rotation into the orthogonal routing space, z = R_h^T v (Sec. 3.2).
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -371,50 +373,150 @@ __global__ __launch_bounds__(256) void k_rotate_bf16(RotateParams p) {
   }
 }
 
-// Vector-ALU rotation for f32 (and any head width): one thread per output.
-template <class T>
-__global__ __launch_bounds__(256) void k_rotate_generic(const T* __restrict__ v, const T* __restrict__ R,
-                                                        T* __restrict__ z, int ntok, int H, int dh) {
-  const int per = 256 / dh;
-  if (static_cast<int>(threadIdx.x) >= per * dh) return;
-  const size_t th = static_cast<size_t>(blockIdx.x) * per + threadIdx.x / dh;
-  if (th >= static_cast<size_t>(ntok) * H) return;
-  const int j = threadIdx.x % dh;
-  const int h = static_cast<int>(th % H);
-  const T* vr = v + th * dh;
-  const T* Rh = R + static_cast<size_t>(h) * dh * dh;
-  float acc = 0.f;
-  for (int k = 0; k < dh; ++k) acc += tof(Rh[k * dh + j]) * tof(vr[k]);
-  z[th * dh + j] = fromf<T>(acc);
-}
-
-// Vector-ALU fused rotation + pack: one thread per output element; the
-// element is stored only if its group is kept.
-template <class T>
-__global__ __launch_bounds__(256) void k_rotate_pack_generic(RotateParams p, int dh) {
-  const int per = 256 / dh;
-  if (static_cast<int>(threadIdx.x) >= per * dh) return;
-  const size_t th = static_cast<size_t>(blockIdx.x) * per + threadIdx.x / dh;
-  if (th >= static_cast<size_t>(p.ntok) * p.H) return;
-  const int j = threadIdx.x % dh;
-  const int h = static_cast<int>(th % p.H);
-  const size_t tok = th / p.H;
-  const int b = static_cast<int>(tok / p.T);
-  const int ds = dh / p.G, g = j / ds;
+// f32 rotation on matrix cores (16x16x4), Z^T = R_h^T V^T. A workgroup stages
+// R_h in LDS (rows padded by 4 floats: the four rows of an A read then fall on
+// two halves of the banks) and its waves take 16-token tiles of one head; the
+// values come straight from memory, 16 bytes per lane (token l16, dims 16kk +
+// 4 g4 ..), as the B operands of four MFMAs whose k = g4 is dim 16kk + 4 g4 + i.
+// A lane ends with 4 consecutive outputs of its token, one 16-byte store (per
+// group of 2 dims, an 8-byte one); with PACK only kept groups, at the slots that
+// the offsets (written beforehand) give. With E = 2 two tiles share an A read.
+// Bound by the f32 matrix rate (32 cycles per MFMA, 64 * DH / 16 of them per
+// tile at DH = 128) and, with few tokens, by staging R_h. Measured (rotate + pack
+// of 354 tokens, 32 heads of 128): 10.7 us against 76 of one thread per output.
+template <int DH, bool PACK, int E>
+__global__ __launch_bounds__(256) void k_rotate_f32(RotateParams p) {
+  constexpr int MT = DH / 16, LD = DH + 4;
+  __shared__ __attribute__((aligned(16))) float Rs[DH * LD];  // R_h [k][j]
+  const int H = p.H, ntok = p.ntok;
+  int h, chunk;
+  xcd_split(blockIdx.x, H, h, chunk);
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t_begin = chunk * p.tok_per_wg, t_end = min(t_begin + p.tok_per_wg, ntok);
+  const uint32_t stride = static_cast<uint32_t>(H) * DH * 4;
+  const uint32_t run_bytes = static_cast<uint32_t>(t_end - t_begin - 1) * stride + DH * 4;
+  const rsrc_t r_v = make_rsrc(static_cast<const float*>(p.v) + (static_cast<size_t>(t_begin) * H + h) * DH, run_bytes);
+  const rsrc_t r_z = make_rsrc(static_cast<float*>(p.z) + (PACK ? 0 : (static_cast<size_t>(t_begin) * H + h) * DH),
+                               PACK ? 0u : run_bytes);
   const uint32_t gm = p.G >= 32 ? 0xFFFFFFFFu : ((1u << p.G) - 1u);
-  const uint32_t m = p.mask[tok] & gm;
-  const int64_t slot = p.offsets[tok + b] + __popc(m & ((1u << g) - 1u));
-  if (!((m >> g) & 1u) || slot >= p.cap) return;
-  const T* vr = static_cast<const T*>(p.v) + th * dh;
-  const T* Rh = static_cast<const T*>(p.R) + static_cast<size_t>(h) * dh * dh;
-  float acc = 0.f;
-  for (int k = 0; k < dh; ++k) acc += tof(Rh[k * dh + j]) * tof(vr[k]);
-  static_cast<T*>(p.Vp)[((static_cast<size_t>(b) * p.H + h) * p.cap + slot) * ds + (j - g * ds)] = fromf<T>(acc);
+  const int ds = DH / p.G, lds = __builtin_ctz(ds);  // a power of two
+
+  struct Tile {
+    u32x4 v[E][MT];
+  };
+  auto load = [&](Tile& x, int tt) {
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int kk = 0; kk < MT; ++kk) {
+        const int tok = tt + 16 * e + l16;
+        x.v[e][kk] = bload16(r_v, oob_unless(tok < t_end, static_cast<uint32_t>(tok - t_begin) * stride + 64u * kk + 16u * g4));
+      }
+  };
+  Tile x;
+  int tt = t_begin + 16 * E * w;
+  load(x, tt);  // in flight while R_h is staged
+  {
+    const rsrc_t r_R = make_rsrc(static_cast<const float*>(p.R) + static_cast<size_t>(h) * DH * DH, DH * DH * 4);
+    constexpr int NI = DH * DH / 4 / 256;
+    u32x4 r[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) r[i] = bload16(r_R, 16u * (tid + 256 * i));
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int e = 4 * (tid + 256 * i);
+      *reinterpret_cast<u32x4*>(Rs + (e / DH) * LD + e % DH) = r[i];
+    }
+  }
+  __syncthreads();
+  for (; tt < t_end; tt += 64 * E) {
+    f32x4 acc[E][MT];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[e][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < MT; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float* a = Rs + (16 * kk + 4 * g4 + i) * LD + l16;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const float av = a[16 * m];
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            acc[e][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, __uint_as_float(x.v[e][kk][i]), acc[e][m], 0, 0, 0);
+        }
+      }
+    load(x, tt + 64 * E);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int tok = tt + 16 * e + l16;
+      const bool in = tok < t_end;
+      if constexpr (!PACK) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(u32x4, acc[e][m]), r_z,
+              oob_unless(in, static_cast<uint32_t>(tok - t_begin) * stride + 64u * m + 16u * g4), 0, 0);
+      } else if (in) {
+        const int b = tok / p.T;
+        const uint32_t mask = p.mask[tok] & gm;
+        const int64_t off = p.offsets[tok + b];
+        float* base = static_cast<float*>(p.Vp) + (static_cast<size_t>(b) * H + h) * p.cap * ds;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const int dim = 16 * m + 4 * g4;
+          if (ds >= 4) {
+            const int g = dim >> lds;
+            const int64_t slot = off + __popc(mask & ((1u << g) - 1u));
+            if (((mask >> g) & 1u) && slot < p.cap) {
+              float* o = base + slot * ds + (dim & (ds - 1));
+#pragma unroll
+              for (int i = 0; i < 4; ++i) o[i] = acc[e][m][i];
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {  // ds = 2: groups dim / 2 and dim / 2 + 1
+              const int g = dim / 2 + u;
+              const int64_t slot = off + __popc(mask & ((1u << g) - 1u));
+              if (((mask >> g) & 1u) && slot < p.cap) {
+                base[slot * 2] = acc[e][m][2 * u];
+                base[slot * 2 + 1] = acc[e][m][2 * u + 1];
+              }
+            }
+          }
+        }
+      }
+    }
+  }
 }
 
 }  // namespace
 
 namespace {
+// f32: two workgroups fit a CU (68 KB of LDS each at dh = 128). Few tokens: one
+// 16-token tile per wave, 64 tokens per workgroup (the serial chain of a tile's
+// MFMAs, 4 us at dh = 128, is what counts); where 128-token workgroups fill the
+// chip, two tiles per wave and runs of up to 512 tokens per staged R_h.
+template <bool PACK>
+hipError_t launch_rotate_f32(RotateParams& p, int dh, hipStream_t s) {
+  int cus = 256, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    cus = 256;
+  const long steps = (static_cast<long>(p.ntok) + 127) / 128 * p.H;
+  const bool two = steps >= 2L * cus;
+  p.tok_per_wg = two ? static_cast<int>(128 * std::min(4L, steps / (2L * cus))) : 64;
+  const dim3 grid(static_cast<unsigned>((static_cast<long>(p.ntok) + p.tok_per_wg - 1) / p.tok_per_wg * p.H));
+  if (dh == 128 && two) hipLaunchKernelGGL((k_rotate_f32<128, PACK, 2>), grid, dim3(256), 0, s, p);
+  else if (dh == 128) hipLaunchKernelGGL((k_rotate_f32<128, PACK, 1>), grid, dim3(256), 0, s, p);
+  else if (two) hipLaunchKernelGGL((k_rotate_f32<64, PACK, 2>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_rotate_f32<64, PACK, 1>), grid, dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
 // workgroups of the matrix-core rotation resident at once: three per CU at
 // dh = 128, four at dh = 64
 long rotate_slots(int dh) {
@@ -451,33 +553,21 @@ int rotate_tokens_per_wg(int ntok, int H, int dh) {
 hipError_t launch_rotate(bool bf16, int ntok, int H, int dh, const void* v, const void* R, void* z,
                          hipStream_t s) {
   if (ntok == 0 || H == 0) return hipSuccess;
-  if (bf16 && (dh == 128 || dh == 64)) {
-    RotateParams p = {};
-    p.ntok = ntok;
-    p.H = H;
-    p.v = v;
-    p.R = R;
-    p.z = z;
-    p.G = 1;
-    p.tok_per_wg = rotate_tokens_per_wg(ntok, H, dh);
-    const dim3 grid(static_cast<unsigned>(((ntok + p.tok_per_wg - 1) / p.tok_per_wg) * H));
-    p.dyn_tiles = static_cast<long>(grid.x) <= rotate_slots(dh) ? 1 : 0;
-    if (dh == 128)
-      hipLaunchKernelGGL((k_rotate_bf16<128, kZ>), grid, dim3(256), 0, s, p);
-    else
-      hipLaunchKernelGGL((k_rotate_bf16<64, kZ>), grid, dim3(256), 0, s, p);
-  } else {
-    const int per = 256 / dh;
-    const size_t n = static_cast<size_t>(ntok) * H;
-    const dim3 grid(static_cast<unsigned>((n + per - 1) / per));
-    if (bf16)
-      hipLaunchKernelGGL(k_rotate_generic<rolesub::bf16>, grid, dim3(256), 0, s,
-                         static_cast<const rolesub::bf16*>(v), static_cast<const rolesub::bf16*>(R),
-                         static_cast<rolesub::bf16*>(z), ntok, H, dh);
-    else
-      hipLaunchKernelGGL(k_rotate_generic<float>, grid, dim3(256), 0, s, static_cast<const float*>(v),
-                         static_cast<const float*>(R), static_cast<float*>(z), ntok, H, dh);
-  }
+  RotateParams p = {};
+  p.ntok = ntok;
+  p.H = H;
+  p.v = v;
+  p.R = R;
+  p.z = z;
+  p.G = 1;
+  if (!bf16) return launch_rotate_f32<false>(p, dh, s);
+  p.tok_per_wg = rotate_tokens_per_wg(ntok, H, dh);
+  const dim3 grid(static_cast<unsigned>(((ntok + p.tok_per_wg - 1) / p.tok_per_wg) * H));
+  p.dyn_tiles = static_cast<long>(grid.x) <= rotate_slots(dh) ? 1 : 0;
+  if (dh == 128)
+    hipLaunchKernelGGL((k_rotate_bf16<128, kZ>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((k_rotate_bf16<64, kZ>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -486,11 +576,9 @@ hipError_t launch_rotate_pack(bool bf16, int B, int T, int H, int dh, int G, con
                               hipStream_t s) {
   const int ntok = B * T;
   if (B == 0) return hipSuccess;
-  const bool mfma = bf16 && (dh == 128 || dh == 64) && dh / G >= 2;
-  // the matrix-core kernel forms the offsets itself for prefixes of at most
-  // kRotMaxRun tokens; otherwise (or when it does not run) they come first
-  // from their own kernel
-  const bool off_ready = !mfma || T > kRotMaxRun;
+  // the bf16 kernel forms the offsets itself for prefixes of at most
+  // kRotMaxRun tokens; otherwise they come first from their own kernel
+  const bool off_ready = !bf16 || T > kRotMaxRun;
   if (off_ready || ntok == 0 || H == 0 || cap == 0) {
     const hipError_t e = launch_pack_offsets(B, T, G, mask, offsets, s);
     if (e != hipSuccess) return e;
@@ -508,31 +596,22 @@ hipError_t launch_rotate_pack(bool bf16, int B, int T, int H, int dh, int G, con
   p.Vp = Vp;
   p.cap = cap;
   p.off_ready = off_ready ? 1 : 0;
-  if (mfma) {
-    p.tok_per_wg = rotate_tokens_per_wg(ntok, H, dh);
-    const dim3 grid(static_cast<unsigned>(((ntok + p.tok_per_wg - 1) / p.tok_per_wg) * H));
-    p.dyn_tiles = static_cast<long>(grid.x) <= rotate_slots(dh) ? 1 : 0;
-    // G <= 32, so 2-dim groups occur only at dh = 64
-    const int ds = dh / G;
-    if (dh == 128 && ds >= 8)
-      hipLaunchKernelGGL((k_rotate_bf16<128, kPack16>), grid, dim3(256), 0, s, p);
-    else if (dh == 128)
-      hipLaunchKernelGGL((k_rotate_bf16<128, kPack8>), grid, dim3(256), 0, s, p);
-    else if (ds >= 8)
-      hipLaunchKernelGGL((k_rotate_bf16<64, kPack16>), grid, dim3(256), 0, s, p);
-    else if (ds == 4)
-      hipLaunchKernelGGL((k_rotate_bf16<64, kPack8>), grid, dim3(256), 0, s, p);
-    else
-      hipLaunchKernelGGL((k_rotate_bf16<64, kPack4>), grid, dim3(256), 0, s, p);
-  } else {
-    const int per = 256 / dh;
-    const size_t n = static_cast<size_t>(ntok) * H;
-    const dim3 grid(static_cast<unsigned>((n + per - 1) / per));
-    if (bf16)
-      hipLaunchKernelGGL(k_rotate_pack_generic<rolesub::bf16>, grid, dim3(256), 0, s, p, dh);
-    else
-      hipLaunchKernelGGL(k_rotate_pack_generic<float>, grid, dim3(256), 0, s, p, dh);
-  }
+  if (!bf16) return launch_rotate_f32<true>(p, dh, s);
+  p.tok_per_wg = rotate_tokens_per_wg(ntok, H, dh);
+  const dim3 grid(static_cast<unsigned>(((ntok + p.tok_per_wg - 1) / p.tok_per_wg) * H));
+  p.dyn_tiles = static_cast<long>(grid.x) <= rotate_slots(dh) ? 1 : 0;
+  // G <= 32, so 2-dim groups occur only at dh = 64
+  const int ds = dh / G;
+  if (dh == 128 && ds >= 8)
+    hipLaunchKernelGGL((k_rotate_bf16<128, kPack16>), grid, dim3(256), 0, s, p);
+  else if (dh == 128)
+    hipLaunchKernelGGL((k_rotate_bf16<128, kPack8>), grid, dim3(256), 0, s, p);
+  else if (ds >= 8)
+    hipLaunchKernelGGL((k_rotate_bf16<64, kPack16>), grid, dim3(256), 0, s, p);
+  else if (ds == 4)
+    hipLaunchKernelGGL((k_rotate_bf16<64, kPack8>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((k_rotate_bf16<64, kPack4>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

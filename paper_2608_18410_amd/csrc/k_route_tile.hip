@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_route_pool_any(RouteParams p) {
 // tile's tokens 16*wave.. as one f32x4 per lane (token l16, rows 4*g4 ..).
 //
 // Both operands stream through a ring of LDS stages of 128 bytes per row (64
-// bf16 or 32 f32 columns), filled by asynchronous LDS DMA issued several stages
+// bf16 or 32 f32 columns), filled by asynchronous LDS DMA issued several
 // stages ahead; rows are stored with their 16-byte pieces XOR-swizzled, which makes
 // the fragment reads of 16 rows free of bank conflicts. A 16-byte piece per
 // lane is one operand of a bf16 16x16x32 MFMA, or of four f32 16x16x4 MFMAs
