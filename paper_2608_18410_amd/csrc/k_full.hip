@@ -18,8 +18,7 @@
 namespace rolesub {
 namespace {
 
-constexpr int kBM0 = 64, kBM1 = 128, kBN = 128, kBK = 64;  // row tiles: rotate, values
-constexpr int kLd = kBK + 8;  // LDS row stride (elements): 144 bytes, conflict-free 16-byte fragment reads
+constexpr int kBN = 128, kBK = 64;  // columns of a tile, k per stage
 constexpr int kPrepChunks = 16;
 
 __device__ __forceinline__ uint32_t full_bits(int S) { return S >= 32 ? 0xFFFFFFFFu : ((1u << S) - 1u); }
@@ -199,62 +198,65 @@ __global__ __launch_bounds__(256) void k_full_prep(FullParams p) {
   }
 }
 
-// C[m][n] = sum_k A[m][k] * Bt[n][k] on 16x16x32 bf16 MFMA; 128 x 128 tile per
-// workgroup, four waves of 64 x 64, k in steps of 64 (two MFMA k-steps per
-// barrier) through a double-buffered LDS tile, the next step's operands in
-// flight in registers.
-// 128-row tiles: about 78 KB of LDS and 224 registers, two workgroups per CU;
-// 64-row tiles: 59 KB, two per CU.
+// C[m][n] = sum_k A[m][k] * Bt[n][k] on 16x16x32 bf16 MFMA, a TBM x 128 tile per
+// workgroup, waves of (TBM / WM) x 64, k in stages of 64.
 //   MODE 0 (rotate): rows are the routed tokens of all samples that keep the
 //   workgroup's group g (per-sample lists from the preparation kernel), so only
 //   kept groups are computed; A = v, Bt = the rows of R^T for group g's output
 //   dims; results to the cache.
 //   MODE 1 (values): rows are the routed tokens of all samples; A = their cached
-//   groups of z~ (zero where dropped; steps of groups that no row of the tile
+//   groups of z~ (zero where dropped; stages of groups that no row of the tile
 //   keeps are skipped), Bt = R; results head-major.
 // Rows map to (sample, token) through the prefix of the per-sample counts.
 // Groups (MODE 0) or column tiles (MODE 1) are pinned to XCDs so that each XCD
 // reads only its share of R into its L2.
-template <int MODE, int TBM, int NS>
-__global__ __launch_bounds__(256, 2) void k_full_gemm(FullParams p) {
-  // A and B tiles (double-buffered) in one region, reused for the output tile
-  constexpr int kTileA = TBM * kLd, kTileB = kBN * kLd;
-  constexpr int NA = TBM / 32, NB = kBN / 32, MI = TBM / 32;  // A, B pieces per thread, 16-row blocks per wave
-  __shared__ __attribute__((aligned(16))) bf16 smem[2 * kTileA + 2 * kTileB];
-  // tile i of A at smem + i * kTileA, of B at smem + 2 * kTileA + i * kTileB
+//
+// Buffer->LDS DMA brings the stages into a ring of RING (operands in flight in
+// registers, two sets of them at most, covered little of the round trip to L2).
+// Rows of 128 bytes, 16-byte chunks XOR-swizzled by row pair (conflict-free
+// fragment reads). One barrier per stage. NCP = 0: every wave issues its share of
+// the DMAs between its MFMAs. NCP > 0: NCP waves do nothing else, since a wave whose
+// DMA waits for the texture unit holds up the MFMAs behind it.
+// Bound by the texture unit, which takes a 128-byte line of a DMA in about 2.6
+// clocks, and for the 256-row tile by that and the MFMAs in turn (a wave that
+// only touches later lines to bring them into L2 made both slower, 52 -> 79 us).
+//
+// Measured at d_v = 4096, 64 prefixes of 81 tokens, 32 of them routed, preparation
+// included, against register staging:
+//   rotate, 4 (8, 15) of 16 groups kept: 73.5 (99.6, 120.6) -> 52.4 (75, 93) us with 64 rows,
+//     three stages, two workgroups per CU; six stages and one per CU: 62 (a group's
+//     last row tile then starts when the others end); with copying waves: 59;
+//   values, 256 rows, eight MFMA and four copying waves: 105 -> 78 us; no
+//     copying waves: 87; 128 rows: 97-118; 64 rows: 121. One prefix (16), 64 rows:
+//     65 (70) -> 37 (41) us, 256 rows: 54 (57). A values product over each group's kept
+//     rows only, with f32 accumulators in LDS, took 140 us (uncoalesced fragments).
+__device__ __forceinline__ int full_swz(int row) { return (row >> 1) & 7; }
+
+template <int MODE, int TBM, int WM, int RING, int NWG, int NCP>
+__global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4) void k_full_gemm(FullParams p) {
+  constexpr int NW = 2 * WM, NT = 64 * NW, NP = NCP ? NCP : NW, MI = TBM / WM / 16;  // MFMA waves, their threads, copying waves, 16-row blocks per wave
+  constexpr int kStA = TBM * kBK * 2, kStB = kBN * kBK * 2, kStage = kStA + kStB;  // bytes
+  constexpr int UA = kStA / 1024 / NP, UB = kStB / 1024 / NP;  // A and B DMAs per copying wave and stage
+  static_assert(kBK == 64 && kStA % (1024 * NP) == 0 && kStB % (1024 * NP) == 0 && RING >= 3, "stage shape");
+  __shared__ __attribute__((aligned(16))) char ring[RING * kStage];
   __shared__ int pre[kFullMaxB + 1];
   __shared__ int r_b[TBM], r_t[TBM], r_off[TBM];
   __shared__ uint32_t r_mask[TBM];
   __shared__ uint32_t s_or;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = p.B, T = p.T, dv = p.dv, S = p.S, ds = p.ds;
   // which tile: (group g, column sub-tile, row tile) or (column tile, row tile)
-  const int lin = blockIdx.x;
-  int g = 0, n0 = 0, mt = 0;
+  int g = 0, n0, mt;
   if (MODE == 0) {
     const int nsub = ds / kBN;
     int rest;
-    if ((S & 7) == 0) {
-      const int xcd = lin & 7, slot = lin >> 3, per = S >> 3;
-      g = xcd + 8 * (slot % per);
-      rest = slot / per;
-    } else {
-      g = lin % S;
-      rest = lin / S;
-    }
+    xcd_split(blockIdx.x, S, g, rest);
     n0 = g * ds + (rest % nsub) * kBN;
     mt = rest / nsub;
   } else {
-    const int ntn = dv / kBN;
     int nt;
-    if ((ntn & 7) == 0) {
-      const int xcd = lin & 7, slot = lin >> 3, per = ntn >> 3;
-      nt = xcd + 8 * (slot % per);
-      mt = slot / per;
-    } else {
-      nt = lin % ntn;
-      mt = lin / ntn;
-    }
+    xcd_split(blockIdx.x, dv / kBN, nt, mt);
     n0 = nt * kBN;
   }
   const int m0 = mt * TBM;
@@ -299,168 +301,163 @@ __global__ __launch_bounds__(256, 2) void k_full_gemm(FullParams p) {
     r_off[tid] = oo;
   }
   __syncthreads();
-  const uint32_t tile_or = MODE == 1 ? s_or : full_bits(S);
+  const uint32_t tile_or = MODE == 1 ? __builtin_amdgcn_readfirstlane(s_or) : full_bits(S);
 
-  // operand sources
+  // DMA j of an operand fills its LDS bytes 1024 j ..: rows 8j .. 8j + 7, lane
+  // i's 16 bytes at row 8j + i / 8, position i % 8, which holds chunk
+  // (i % 8) ^ full_swz(row). Copying wave pw issues DMAs pw, pw + NP, ...
+  const int pw = NCP ? max(w - NW, 0) : w;  // (unused in MFMA waves of NCP > 0)
   const rsrc_t r_A = MODE == 0
       ? make_rsrc(p.v, clamp_bytes(static_cast<size_t>(B) * T * dv * 2))
       : make_rsrc(p.Vp, clamp_bytes(static_cast<size_t>(B) * p.cap * ds * 2));
   const rsrc_t r_B = make_rsrc(p.Rm, clamp_bytes(static_cast<size_t>(dv) * dv * 2));
-  // this thread's NA A pieces and NB B pieces per step: piece q = tid + 256 u,
-  // row q / 8, 16-byte chunk q % 8
-  constexpr int NP = NA > NB ? NA : NB;
-  int arow[NP], ach[NP];
+  // A rows: MODE 0 the byte offset of the token's value row, MODE 1 the byte
+  // offset of the sample's cache and the token's mask and first slot
+  uint32_t a_base[UA], a_mask[UA], b_base[UB];
+  int a_slot0[UA];
+  bool a_ok[UA];
 #pragma unroll
-  for (int u = 0; u < NP; ++u) {
-    arow[u] = (tid + 256 * u) >> 3;
-    ach[u] = (tid + 256 * u) & 7;
-  }
-  // this thread's A rows, read once: MODE 0 the byte offset of the token's
-  // value row, MODE 1 the byte offset of the sample's cache and the token's
-  // mask and first slot
-  uint32_t a_base[NA], a_mask[NA];
-  int a_slot0[NA];
-  bool a_ok[NA];
-#pragma unroll
-  for (int u = 0; u < NA; ++u) {
-    const int row = arow[u];
-    const int bb = r_b[row];
+  for (int u = 0; u < UA; ++u) {
+    const int row = 8 * (pw + NP * u) + (lane >> 3), bb = r_b[row];
+    const uint32_t ch = 16u * ((lane & 7) ^ full_swz(row));
     a_ok[u] = bb >= 0;
     a_mask[u] = r_mask[row];
     a_slot0[u] = r_off[row];
-    a_base[u] = MODE == 0 ? static_cast<uint32_t>(((static_cast<size_t>(bb < 0 ? 0 : bb) * T + r_t[row]) * dv + 8 * ach[u]) * 2)
-                          : static_cast<uint32_t>((static_cast<size_t>(bb < 0 ? 0 : bb) * p.cap * ds + 8 * ach[u]) * 2);
+    a_base[u] = ch + (MODE == 0 ? static_cast<uint32_t>((static_cast<size_t>(bb < 0 ? 0 : bb) * T + r_t[row]) * dv * 2)
+                                : static_cast<uint32_t>(static_cast<size_t>(bb < 0 ? 0 : bb) * p.cap * ds * 2));
   }
-  auto a_off = [&](int u, int k0) -> uint32_t {
-    if (MODE == 0) {
-      return oob_unless(a_ok[u], a_base[u] + static_cast<uint32_t>(k0) * 2u);
-    } else {
-      const int g = k0 / ds;
-      const int slot = a_slot0[u] + __popc(a_mask[u] & ((1u << g) - 1u));
-      const bool ok = a_ok[u] && ((a_mask[u] >> g) & 1u) && slot < p.cap;
-      return oob_unless(ok, a_base[u] + static_cast<uint32_t>((slot * ds + (k0 - g * ds)) * 2));
-    }
-  };
-  auto b_off = [&](int u, int k0) -> uint32_t {
-    const size_t e = static_cast<size_t>(n0 + arow[u]) * dv + k0 + 8 * ach[u];
-    return static_cast<uint32_t>(e * 2);
-  };
-  // k steps: every step of every group in tile_or (MODE 0: all groups);
-  // branch-free, and k >= dv stays at dv (loads past the end read zeros)
+#pragma unroll
+  for (int u = 0; u < UB; ++u) {
+    const int row = 8 * (pw + NP * u) + (lane >> 3);
+    b_base[u] = static_cast<uint32_t>(static_cast<size_t>(n0 + row) * dv * 2) + 16u * ((lane & 7) ^ full_swz(row));
+  }
+  const int cap32 = static_cast<int>(p.cap);  // < 2^31: a sample's cache is < 2 GiB
+  const uint32_t ring_base = lds_addr(ring);
+  // k of the stages: every stage of every group in tile_or (MODE 0: all groups);
+  // past the last, k stays at dv and the DMAs are out of range (they write zeros
+  // to a free stage), so the number of pending ones stays known
   auto next_k = [&](int k0) -> int {
     const int k1 = k0 + kBK;
+    if (k0 >= dv) return dv;
+    if (MODE == 0 || k1 % ds != 0) return k1;
     const int gb = k1 / ds;
     const uint32_t rest = gb < 32 ? (tile_or >> gb) : 0u;
-    const int kg = rest ? (gb + static_cast<int>(__builtin_ctz(rest))) * ds : dv;
-    const int kn = (k1 % ds != 0) ? k1 : kg;
-    return k0 >= dv ? dv : (kn < dv ? kn : dv);
+    return rest ? (gb + static_cast<int>(__builtin_ctz(rest))) * ds : dv;
   };
-  const int k_first = tile_or == 0 ? dv : static_cast<int>(__builtin_ctz(tile_or)) * ds;
-  // active steps: a multiple of 2 (ds is a multiple of 128: at least 2 steps
-  // per group), which NS divides. Steps of 64 columns (two MFMA k-steps per
-  // barrier) took the values product from 110-121 to 100-109 us (prep
-  // included) with two operand sets; more sets were slower for both products
-  // (the rotation: 107 us with four sets of 64 columns, 104 with eight of 32,
-  // against 72-77).
-  const int nsteps = MODE == 0 ? dv / kBK : __popc(tile_or) * (ds / kBK);
+  int kq = tile_or == 0 ? dv : static_cast<int>(__builtin_ctz(tile_or)) * ds;
+  const int nst = MODE == 0 ? dv / kBK : __popc(tile_or) * (ds / kBK);
+  auto issue = [&](int buf, int k0, int u) {
+    const uint32_t dst = ring_base + buf * kStage;
+    const bool real = k0 < dv;
+    if (u < UA) {
+      uint32_t off;
+      bool ok = real & a_ok[u];
+      if (MODE == 0) {
+        off = a_base[u] + 2u * k0;
+      } else {
+        const int gk = min(k0 / ds, 31);
+        const int slot = a_slot0[u] + __popc(a_mask[u] & ((1u << gk) - 1u));
+        ok = ok & ((a_mask[u] >> gk) & 1u) & (slot < cap32);
+        off = a_base[u] + static_cast<uint32_t>((slot * ds + (k0 - gk * ds)) * 2);
+      }
+      dma16(r_A, oob_unless(ok, off), dst + 1024u * (pw + NP * u));
+    } else {
+      dma16(r_B, oob_unless(real, b_base[u - UA] + 2u * k0), dst + kStA + 1024u * (pw + NP * (u - UA)));
+    }
+  };
+  auto fill_ring = [&]() {
+#pragma unroll
+    for (int s = 0; s < RING; ++s) {
+#pragma unroll
+      for (int u = 0; u < UA + UB; ++u) issue(s, kq, u);
+      kq = next_k(kq);
+    }
+    wait_vmcnt<(UA + UB) * (RING - 1)>();  // the first stage
+  };
+  if (NCP && w >= NW) {
+    // copying wave: the barriers of the MFMA waves, below
+    fill_ring();
+    __syncthreads();
+    for (int s = 0, cur = 0; s < nst; ++s) {
+      wait_vmcnt<(UA + UB) * (RING - 2)>();  // stage s + 1: RING - 2 younger ones may be pending
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < UA + UB; ++u) issue(cur, kq, u);
+      kq = next_k(kq);
+      cur = cur + 1 == RING ? 0 : cur + 1;
+    }
+    wait_vmcnt<0>();  // trailing out-of-range DMAs land before the ring is reused
+    __syncthreads();
+    __syncthreads();
+    return;
+  }
+  if (!NCP) fill_ring();
 
-  // the loop body covers NS steps and picks the LDS buffer by step parity:
-  // NS must be even and divide the step count
-  static_assert(NS == 2 || NS == 4, "operand sets: even and a divisor of 4");
   f32x4 acc[MI][4];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
   const int wm = w >> 1, wn = w & 1;
-  // NS register sets: step s's operands arrive in set s % NS, issued NS - 1
-  // steps before they are written to LDS
-  u32x4 ra[NS][NA], rbv[NS][NB];
-  // MODE 1 computes the offsets unconditionally: with a branch around its
-  // (longer) address computation the compiler reuses an in-flight load's
-  // registers and waits for every load (values 117.6 -> 110.4 us). The
-  // rotation's short computation is faster with the select (71.7 vs 82.2 us;
-  // both measured in one process).
-  auto load_set = [&](u32x4 (&a)[NA], u32x4 (&bb)[NB], int k0) {
-    const bool real = k0 < dv;
-    if constexpr (MODE == 1) {
-      const int kk = real ? k0 : 0;
+  struct Frags {
+    bf16x8 a[MI], b[4];
+  };
+  auto read = [&](Frags& f, int buf, int ks) {
+    const char* st = ring + buf * kStage;
 #pragma unroll
-      for (int u = 0; u < NA; ++u) a[u] = bload16(r_A, oob_unless(real, a_off(u, kk)));
+    for (int i = 0; i < MI; ++i) {
+      const int r = (TBM / WM) * wm + 16 * i + l16;
+      f.a[i] = *reinterpret_cast<const bf16x8*>(st + r * 128 + 16 * ((4 * ks + g4) ^ full_swz(r)));
+    }
 #pragma unroll
-      for (int u = 0; u < NB; ++u) bb[u] = bload16(r_B, oob_unless(real, b_off(u, kk)));
-    } else {
-#pragma unroll
-      for (int u = 0; u < NA; ++u) a[u] = bload16(r_A, real ? a_off(u, k0) : kOOB);
-#pragma unroll
-      for (int u = 0; u < NB; ++u) bb[u] = bload16(r_B, real ? b_off(u, k0) : kOOB);
+    for (int j = 0; j < 4; ++j) {
+      const int r = 64 * wn + 16 * j + l16;
+      f.b[j] = *reinterpret_cast<const bf16x8*>(st + kStA + r * 128 + 16 * ((4 * ks + g4) ^ full_swz(r)));
     }
   };
-  auto store_set = [&](const u32x4 (&a)[NA], const u32x4 (&bb)[NB], int buf) {
-#pragma unroll
-    for (int u = 0; u < NA; ++u)
-      *reinterpret_cast<u32x4*>(&(smem + buf * kTileA)[arow[u] * kLd + 8 * ach[u]]) = a[u];
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-      *reinterpret_cast<u32x4*>(&(smem + 2 * kTileA + buf * kTileB)[arow[u] * kLd + 8 * ach[u]]) = bb[u];
-  };
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int ks = 0; ks < kBK / 32; ++ks) {
-      bf16x8 af[MI], bfr[4];
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-        af[i] = *reinterpret_cast<const bf16x8*>(
-            &(smem + buf * kTileA)[((TBM / 2) * wm + 16 * i + l16) * kLd + 32 * ks + 8 * g4]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        bfr[i] = *reinterpret_cast<const bf16x8*>(
-            &(smem + 2 * kTileA + buf * kTileB)[(64 * wn + 16 * i + l16) * kLd + 32 * ks + 8 * g4]);
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mfma_16x16x32(af[i], bfr[j], acc[i][j]);
-    }
-  };
-  // prologue: steps 0..NS-1 issued in the same order the loop keeps
-  int kq = k_first;
-#pragma unroll
-  for (int j = 0; j < NS - 1; ++j) {
-    load_set(ra[j], rbv[j], kq);
-    kq = next_k(kq);
-  }
-  store_set(ra[0], rbv[0], 0);
-  load_set(ra[NS - 1], rbv[NS - 1], kq);
-  kq = next_k(kq);
+  // A stage's two MFMA k-steps run one half stage behind their fragment reads.
+  // When every wave has read a stage's second half (the barrier in its middle),
+  // the DMAs of the stage RING further on refill its buffer, spread between MFMAs.
+  Frags f0, f1;
   __syncthreads();
-  for (int s = 0; s < nsteps; s += NS) {
+  read(f0, 0, 0);
+  int cur = 0;
+  for (int s = 0; s < nst; ++s) {
+    read(f1, cur, 1);
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-      // set j is free (step s+j is in LDS): step s+j+NS into it
-      load_set(ra[j], rbv[j], kq);
-      kq = next_k(kq);
-      compute(j & 1);
-      store_set(ra[(j + 1) % NS], rbv[(j + 1) % NS], (j + 1) & 1);
-      __syncthreads();
+    for (int q = 0; q < 4 * MI; ++q) acc[q / 4][q % 4] = mfma_16x16x32(f0.a[q / 4], f0.b[q % 4], acc[q / 4][q % 4]);
+    if (!NCP) wait_vmcnt<(UA + UB) * (RING - 2)>();  // as a copying wave
+    __syncthreads();
+    const int nxt = cur + 1 == RING ? 0 : cur + 1;
+    read(f0, nxt, 0);
+#pragma unroll
+    for (int q = 0; q < 4 * MI; ++q) {
+      acc[q / 4][q % 4] = mfma_16x16x32(f1.a[q / 4], f1.b[q % 4], acc[q / 4][q % 4]);
+#pragma unroll
+      for (int u = 0; u < UA + UB; ++u)
+        if (!NCP && u * 4 * MI / (UA + UB) == q) issue(cur, kq, u);
     }
+    if (!NCP) kq = next_k(kq);
+    cur = nxt;
   }
+  wait_vmcnt<0>();  // as a copying wave
+  __syncthreads();
 
   // stage the bf16 tile in LDS (row stride kBN + 8), then 16-byte stores
   constexpr int kCs = kBN + 8;
-  static_assert(TBM * kCs <= 2 * kTileA + 2 * kTileB, "C tile fits the A and B buffers");
-  bf16* Cs = smem;
+  static_assert(TBM * kCs * 2 <= RING * kStage, "C tile fits the ring");
+  bf16* Cs = reinterpret_cast<bf16*>(ring);
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        Cs[((TBM / 2) * wm + 16 * i + 4 * g4 + e) * kCs + 64 * wn + 16 * j + l16] = static_cast<bf16>(acc[i][j][e]);
+        Cs[((TBM / WM) * wm + 16 * i + 4 * g4 + e) * kCs + 64 * wn + 16 * j + l16] = static_cast<bf16>(acc[i][j][e]);
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < TBM * kBN / 8 / 256; ++u) {
-    const int q = tid + 256 * u, row = q / (kBN / 8), c = q % (kBN / 8);
+  for (int u = 0; u < TBM * kBN / 8 / NT; ++u) {
+    const int q = tid + NT * u, row = q / (kBN / 8), c = q % (kBN / 8);
     const int bb = r_b[row];
     if (bb < 0) continue;
     const u32x4 val = *reinterpret_cast<const u32x4*>(&Cs[row * kCs + 8 * c]);
@@ -498,19 +495,21 @@ hipError_t launch_full(const FullParams& p, int mode, hipStream_t s) {
   const size_t shm_pack = 4 * static_cast<size_t>(p.T + 1) + 4 * static_cast<size_t>(p.T) + 2 * static_cast<size_t>(p.T);
   const size_t shm_vals = 4 * static_cast<size_t>(p.T + 1) + 2 * static_cast<size_t>(p.T);
   // row tiles: at most every token of every sample is a row (upper bound;
-  // tiles past the actual count return at once). The rotation has fewer rows
-  // per group than the values step has in all, so it takes 64-row tiles.
+  // tiles past the actual count return at once). Values: 256-row tiles need many
+  // rows to fill the chip. At 81 tokens a sample, 32 of them routed, the product of
+  // 64-row and 256-row tiles took 37 and 54 us for 1 sample, 41 and 57 for 16, 56
+  // and 59 for 20, 60 and 61 for 32, 84 and 62 for 40; the line lies lower than the
+  // crossing because more of the tokens may be routed.
   const size_t rows = static_cast<size_t>(p.B) * p.T;
+  const unsigned ncol = static_cast<unsigned>(p.dv / kBN);
+  auto tiles = [&](int tbm) { return dim3(ncol * static_cast<unsigned>((rows + tbm - 1) / tbm)); };
   if (mode == 0) {
     hipLaunchKernelGGL(k_full_prep<true>, gprep, dim3(256), shm_pack, s, p);
-    const unsigned ncol = static_cast<unsigned>(p.S * (p.ds / kBN));
-    const unsigned nmt = static_cast<unsigned>((rows + kBM0 - 1) / kBM0);
-    hipLaunchKernelGGL((k_full_gemm<0, kBM0, 2>), dim3(ncol * nmt), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
   } else {
     hipLaunchKernelGGL(k_full_prep<false>, gprep, dim3(256), shm_vals, s, p);
-    const unsigned ntn = static_cast<unsigned>(p.dv / kBN);
-    const unsigned nmt = static_cast<unsigned>((rows + kBM1 - 1) / kBM1);
-    hipLaunchKernelGGL((k_full_gemm<1, kBM1, 2>), dim3(ntn * nmt), dim3(256), 0, s, p);
+    if (rows <= 1536) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((k_full_gemm<1, 256, 4, 3, 1, 4>), tiles(256), dim3(768), 0, s, p);
   }
   return hipGetLastError();
 }

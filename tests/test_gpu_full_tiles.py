@@ -1,0 +1,63 @@
+"""The full-width products at the edges of their tiles: 64 rows per group in the
+rotation, 128 or 64 routed tokens (S above 16) per values tile with the kept
+rows of each group in blocks of 16, steps of 256 or 128 dims, and slots past
+the cache's capacity."""
+import pytest
+import torch
+
+import paper_2608_18410_amd as rs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("H,S,B,T,keep", [
+    (1, 1, 1, 1, 0.5),      # one group of one head, one token
+    (8, 8, 1, 16, 0.5),     # steps of 128 dims, one block
+    (8, 4, 1, 63, 0.3),     # steps of 256, just under a rotation tile of rows
+    (6, 6, 3, 43, 0.7),     # one row past a values tile; group count not a multiple of 8
+    (24, 8, 2, 65, 0.4),    # groups of 384 dims: three steps of 128
+    (8, 1, 2, 70, 0.5),     # one group: its routed tokens keep nothing
+    (16, 2, 2, 64, 0.5),    # groups of 1024 dims: four steps of 256
+    (32, 32, 2, 33, 0.06),  # the 64-row tile, most groups with under 16 rows
+    (32, 32, 1, 130, 0.9),  # the 64-row tile, nearly dense
+])
+@pytest.mark.parametrize("short", [False, True])
+def test_full_products(H, S, B, T, keep, short):
+    g = torch.Generator(device=DEV).manual_seed(1000 * H + 10 * S + T)
+    dv, ds = H * 128, H * 128 // S
+    v = torch.randn((B, T, H, 128), generator=g, device=DEV).bfloat16()
+    R = (torch.randn((dv, dv), generator=g, device=DEV) * dv ** -0.5).bfloat16()
+    kept = torch.rand((B, T, S), generator=g, device=DEV) < keep
+    kept[:, T // 2] = True          # a value-space token per sample
+    mask = (kept.long() << torch.arange(S, device=DEV)).sum(-1).to(torch.uint32)
+    n = kept.sum((1, 2))
+    cap = max(1, int(n.max()) - 2) if short else T * S
+    print(f"full products H={H} S={S} B={B} T={T} cap={cap}", flush=True)
+    off = torch.zeros((B, T + 1), dtype=torch.int32, device=DEV)
+    Vp = torch.zeros((B, cap, ds), dtype=torch.bfloat16, device=DEV)
+    rs.full_rotate_pack(v, rs.full_transpose(R), mask, S, cap, out=(off, Vp))
+    Vh = rs.full_values(R, mask, off, Vp, S, H)
+    torch.cuda.synchronize()
+
+    full = kept.all(-1)
+    v64, R64 = v.reshape(B, T, dv).double(), R.double()
+    z = torch.where(full[..., None], v64, v64 @ R64).reshape(B, T, S, ds)
+    want_off = torch.cat((torch.zeros((B, 1), device=DEV), kept.sum(-1).cumsum(1)), 1).int()
+    assert torch.equal(off, want_off)
+    for b in range(B):
+        zb = z[b][kept[b]]
+        m = min(cap, zb.shape[0])
+        # one rounding to bf16 (2^-9 of the value) and f32 sums of dv products
+        # (at most dv 2^-24 of their magnitudes' sum, which is below sqrt(dv) here)
+        d = (Vp[b, :m].double() - zb[:m]).abs()
+        assert (d <= 2.0 ** -8 * zb[:m].abs() + dv ** 1.5 * 2.0 ** -24).all()
+        assert (Vp[b, m:] == 0).all()
+        # the values step from the cache as stored (slots past it read as zero)
+        zc = torch.zeros((T * S, ds), dtype=torch.float64, device=DEV)
+        where = kept[b].reshape(-1).nonzero()[:m, 0]
+        zc[where] = Vp[b, :m].double()
+        zc = zc.reshape(T, dv)
+        want = torch.where(full[b][:, None], zc, zc @ R64.T).reshape(T, H, 128).transpose(0, 1)
+        d = (Vh[b].double() - want).abs()
+        assert (d <= 2.0 ** -8 * want.abs() + dv ** 1.5 * 2.0 ** -24).all()
