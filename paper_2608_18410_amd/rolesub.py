@@ -108,31 +108,41 @@ def status_name(status: int) -> str:
     return load().rolesub_status_str(status).decode()
 
 
+# A layer at small batches is bound by the host work of its calls, so the checks
+# below take a short way when everything is in order (shapes compared as whole
+# tuples, raw addresses and stream handles, one constructor per struct); what fails
+# it is looked at in detail.
+_Tensor = torch.Tensor
+_I32x4 = ctypes.c_int32 * 4
+
+
 def _check(fn: str, status: int) -> None:
     if status != 0:
         raise RolesubError(fn, status, load().rolesub_last_error().decode())
 
 
+_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    c = _CODES.get(t.dtype)
+    if c is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return c
 
 
 def _ptr(t, dtype=None):
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _Tensor):
         raise TypeError("expected a torch tensor")
     if not t.is_cuda:
         raise ValueError("librolesub takes device tensors only")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"expected {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _fmt(shape):
@@ -145,10 +155,19 @@ def _need(name, t, shape, dtype=None):
     otherwise read or write past a wrongly sized buffer."""
     if t is None:
         return
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _Tensor):
         raise TypeError(f"{name}: expected a torch tensor, got {type(t).__name__}")
-    if t.dim() != len(shape) or any(s is not None and int(s) != int(x) for s, x in zip(shape, t.shape)):
-        raise ValueError(f"{name}: expected shape {_fmt(shape)}, got {list(t.shape)}")
+    if t.shape == shape and (dtype is None or t.dtype is dtype):
+        return
+    got = t.shape
+    ok = len(got) == len(shape)
+    if ok:
+        for want, x in zip(shape, got):
+            if want is not None and want != x and int(want) != int(x):
+                ok = False
+                break
+    if not ok:
+        raise ValueError(f"{name}: expected shape {_fmt(shape)}, got {list(got)}")
     if dtype is not None:
         ok = dtype if isinstance(dtype, tuple) else (dtype,)
         if t.dtype not in ok:
@@ -159,9 +178,15 @@ _MASK = (torch.int32, torch.uint32)
 
 
 def _same_device(*ts):
-    devs = {t.device for t in ts if isinstance(t, torch.Tensor)}
-    if len(devs) > 1:
-        raise ValueError(f"tensors on different devices: {sorted(str(d) for d in devs)}")
+    first = None
+    for t in ts:
+        if isinstance(t, _Tensor):
+            d = t.device
+            if first is None:
+                first = d
+            elif d != first:
+                devs = {t.device for t in ts if isinstance(t, _Tensor)}
+                raise ValueError(f"tensors on different devices: {sorted(str(d) for d in devs)}")
 
 
 def _need_workspace(t):
@@ -170,8 +195,10 @@ def _need_workspace(t):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        # torch.cuda.current_stream().cuda_stream without the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def make_budget(mode=TOPK, k_by_type=(0, 0, 0, 0), tau=0.0, kmin=0, kmax=0) -> Budget:
@@ -195,12 +222,8 @@ class Router:
     alpha_lang: float = 0.1
 
     def desc(self) -> RouterDesc:
-        r = RouterDesc()
-        r.kind, r.C, r.d_e, r.Hr = self.kind, self.C, self.d_e, self.Hr
-        r.alpha_role, r.alpha_lang = self.alpha_role, self.alpha_lang
-        for name, t in self.tensors.items():
-            setattr(r, name, _ptr(t).value)
-        return r
+        return RouterDesc(self.kind, self.C, self.d_e, self.Hr, self.alpha_role, self.alpha_lang,
+                          **{name: _ptr(t) for name, t in self.tensors.items()})
 
     def check(self, d: int, G: int, dtype) -> None:
         """Weight shapes against the hidden size d and G groups (row-major [out][in])."""
@@ -214,7 +237,9 @@ class Router:
         for name, shape in shapes.items():
             if name not in t:
                 raise ValueError(f"router: missing {name}")
-            _need(f"router.{name}", t[name], shape, dtype)
+            w = t[name]
+            if not isinstance(w, _Tensor) or w.shape != shape or w.dtype is not dtype:
+                _need(f"router.{name}", w, shape, dtype)
 
     @staticmethod
     def mlp2(W_r, b_r, E, W1, b1, W2, b2) -> "Router":
@@ -268,7 +293,9 @@ def route(token_type: torch.Tensor, budget: Budget, G: int, h: torch.Tensor | No
     o = out or {}
     for name, shape, dt in (("mask", (B, T), _MASK), ("idx", (B, T, G), torch.uint8),
                             ("count", (B, T), torch.uint8), ("scores", (B, T, G), torch.float32)):
-        _need(f"out[{name!r}]", o.get(name), shape, dt)
+        x = o.get(name)
+        if x is not None and (not isinstance(x, _Tensor) or x.shape != shape or x.dtype is not dt):
+            _need(f"out[{name!r}]", x, shape, dt)
     _need_workspace(workspace)
     _same_device(token_type, h, scores_in, workspace, *o.values())
 
@@ -285,8 +312,8 @@ def route(token_type: torch.Tensor, budget: Budget, G: int, h: torch.Tensor | No
     desc = router.desc() if router is not None else None
     ws_ptr, ws_bytes = None, 0
     if scores_in is None and router is not None:
-        ws_bytes = load().rolesub_route_workspace_size(ctypes.byref(dims), ctypes.byref(desc))
         if workspace is None:
+            ws_bytes = load().rolesub_route_workspace_size(ctypes.byref(dims), ctypes.byref(desc))
             workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
         ws_ptr, ws_bytes = _ptr(workspace), workspace.numel()
     _check("rolesub_route", load().rolesub_route(
@@ -314,7 +341,9 @@ def route_noalloc(token_type: torch.Tensor, budget: Budget, G: int, h: torch.Ten
         raise ValueError("out['mask'] is required")
     for name, shape, dt in (("mask", (B, T), _MASK), ("idx", (B, T, G), torch.uint8),
                             ("count", (B, T), torch.uint8), ("scores", (B, T, G), torch.float32)):
-        _need(f"out[{name!r}]", out.get(name), shape, dt)
+        x = out.get(name)
+        if x is not None and (not isinstance(x, _Tensor) or x.shape != shape or x.dtype is not dt):
+            _need(f"out[{name!r}]", x, shape, dt)
     _same_device(token_type, h, scores_in, *out.values())
     dims = Dims(B, T, 1, 64, G, d)
     desc = router.desc() if router is not None else None
@@ -340,7 +369,7 @@ def pack_kv(z: torch.Tensor, mask: torch.Tensor, G: int, cap: int, budget: Budge
     offsets = torch.empty((B, T + 1), dtype=torch.int32, device=z.device) if out is None else out[0]
     Vp = torch.empty((B, H, cap, ds), dtype=z.dtype, device=z.device) if out is None else out[1]
     dims = Dims(B, T, H, dh, G, 0)
-    tc = (ctypes.c_int32 * 4)(*type_counts) if type_counts is not None else None
+    tc = _I32x4(*type_counts) if type_counts is not None else None
     _check("rolesub_pack_kv", load().rolesub_pack_kv(
         ctypes.byref(dims), _code(z), ctypes.byref(budget) if budget is not None else None, tc,
         _ptr(z), _ptr(mask), _ptr(offsets, torch.int32), _ptr(Vp, z.dtype), int(cap), _stream(stream)))
@@ -362,7 +391,7 @@ def rotate_pack(v: torch.Tensor, R: torch.Tensor, mask: torch.Tensor, G: int, ca
     offsets = torch.empty((B, T + 1), dtype=torch.int32, device=v.device) if out is None else out[0]
     Vp = torch.empty((B, H, cap, ds), dtype=v.dtype, device=v.device) if out is None else out[1]
     dims = Dims(B, T, H, dh, G, 0)
-    tc = (ctypes.c_int32 * 4)(*type_counts) if type_counts is not None else None
+    tc = _I32x4(*type_counts) if type_counts is not None else None
     _check("rolesub_rotate_pack", load().rolesub_rotate_pack(
         ctypes.byref(dims), _code(v), ctypes.byref(budget) if budget is not None else None, tc,
         _ptr(v), _ptr(R, v.dtype), _ptr(mask), _ptr(offsets, torch.int32), _ptr(Vp, v.dtype), int(cap),
@@ -463,7 +492,9 @@ def allocate_groups(priority, token_type, k_by_type, G: int, scores=None, *, wan
     o = out or {}
     for name, shape, dt in (("k", (B, T), torch.uint8), ("mask", (B, T), _MASK), ("idx", (B, T, G), torch.uint8),
                             ("count", (B, T), torch.uint8)):
-        _need(f"out[{name!r}]", o.get(name), shape, dt)
+        x = o.get(name)
+        if x is not None and (not isinstance(x, _Tensor) or x.shape != shape or x.dtype is not dt):
+            _need(f"out[{name!r}]", x, shape, dt)
     _same_device(token_type, priority, scores, *o.values())
 
     def buf(name, shape, dtype, want=True):
@@ -476,7 +507,7 @@ def allocate_groups(priority, token_type, k_by_type, G: int, scores=None, *, wan
     mask = buf("mask", (B, T), torch.int32, sel)
     idx = buf("idx", (B, T, G), torch.uint8, sel and want_idx)
     cnt = buf("count", (B, T), torch.uint8, sel and want_count)
-    kby = (ctypes.c_int32 * 4)(*[int(x) for x in k_by_type])
+    kby = _I32x4(*[int(x) for x in k_by_type])
     _check("rolesub_allocate_groups", load().rolesub_allocate_groups(
         B, T, G, kby, _ptr(priority, torch.float32), _ptr(token_type, torch.uint8), _ptr(scores, torch.float32),
         _ptr(kk), _ptr(mask), _ptr(idx), _ptr(cnt), _stream(stream)))
@@ -506,7 +537,9 @@ def route_allocate(token_type, k_by_type, G: int, h, router: Router, w_pri, *, w
     for name, shape, dt in (("mask", (B, T), _MASK), ("idx", (B, T, G), torch.uint8), ("count", (B, T), torch.uint8),
                             ("k", (B, T), torch.uint8), ("scores", (B, T, G), torch.float32),
                             ("priority", (B, T), torch.float32)):
-        _need(f"out[{name!r}]", o.get(name), shape, dt)
+        x = o.get(name)
+        if x is not None and (not isinstance(x, _Tensor) or x.shape != shape or x.dtype is not dt):
+            _need(f"out[{name!r}]", x, shape, dt)
     _need_workspace(workspace)
     _same_device(token_type, h, w_pri, workspace, *o.values())
 
@@ -523,10 +556,10 @@ def route_allocate(token_type, k_by_type, G: int, h, router: Router, w_pri, *, w
     pri = buf("priority", (B, T), torch.float32, want_priority)
     dims = Dims(B, T, 1, 64, G, d)
     desc = router.desc()
-    ws_bytes = load().rolesub_route_allocate_workspace_size(ctypes.byref(dims), ctypes.byref(desc))
     if workspace is None:
+        ws_bytes = load().rolesub_route_allocate_workspace_size(ctypes.byref(dims), ctypes.byref(desc))
         workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
-    kby = (ctypes.c_int32 * 4)(*[int(x) for x in k_by_type])
+    kby = _I32x4(*[int(x) for x in k_by_type])
     _check("rolesub_route_allocate", load().rolesub_route_allocate(
         ctypes.byref(dims), F32 if h.dtype == torch.float32 else BF16, ctypes.byref(desc), _ptr(w_pri, h.dtype),
         kby, _ptr(h), _ptr(token_type, torch.uint8), _ptr(pri), _ptr(sco), _ptr(kk), _ptr(mask), _ptr(idx),
@@ -574,7 +607,7 @@ def full_rotate_pack(v, Rt, mask, S: int, cap: int, budget: Budget | None = None
     offsets, Vp = out
     if workspace is None:
         workspace = torch.empty(max(full_workspace_size(B, T, S), 1), dtype=torch.uint8, device=v.device)
-    tc = (ctypes.c_int32 * 4)(*[int(x) for x in type_counts]) if type_counts is not None else None
+    tc = _I32x4(*[int(x) for x in type_counts]) if type_counts is not None else None
     dims = Dims(B, T, H, dh, S, 0)
     _check("rolesub_full_rotate_pack", load().rolesub_full_rotate_pack(
         ctypes.byref(dims), _code(v), _ptr(Rt, v.dtype), _ptr(v), _ptr(mask), _ptr(offsets, torch.int32),
