@@ -217,6 +217,7 @@ __global__ __launch_bounds__(256) void k_full_prep(FullParams p) {
 // fragment reads). One barrier per stage. NCP = 0: every wave issues its share of
 // the DMAs between its MFMAs. NCP > 0: NCP waves do nothing else, since a wave whose
 // DMA waits for the texture unit holds up the MFMAs behind it.
+// Operands off 16-byte boundaries (DMA = false) go through registers instead.
 // Bound by the texture unit, which takes a 128-byte line of a DMA in about 2.6
 // clocks, and for the 256-row tile by that and the MFMAs in turn (a wave that
 // only touches later lines to bring them into L2 made both slower, 52 -> 79 us).
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256) void k_full_prep(FullParams p) {
 //     rows only, with f32 accumulators in LDS, took 140 us (uncoalesced fragments).
 __device__ __forceinline__ int full_swz(int row) { return (row >> 1) & 7; }
 
-template <int MODE, int TBM, int WM, int RING, int NWG, int NCP>
+template <int MODE, int TBM, int WM, int RING, int NWG, int NCP, bool DMA = true>
 __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4) void k_full_gemm(FullParams p) {
   constexpr int NW = 2 * WM, NT = 64 * NW, NP = NCP ? NCP : NW, MI = TBM / WM / 16;  // MFMA waves, their threads, copying waves, 16-row blocks per wave
   constexpr int kStA = TBM * kBK * 2, kStB = kBN * kBK * 2, kStage = kStA + kStB;  // bytes
@@ -346,8 +347,12 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
   };
   int kq = tile_or == 0 ? dv : static_cast<int>(__builtin_ctz(tile_or)) * ds;
   const int nst = MODE == 0 ? dv / kBK : __popc(tile_or) * (ds / kBK);
+  auto copy = [&](rsrc_t r, uint32_t off, uint32_t to) {
+    if constexpr (DMA) dma16(r, off, ring_base + to);
+    else *reinterpret_cast<u32x4*>(ring + to + 16 * lane) = bload16(r, off);
+  };
   auto issue = [&](int buf, int k0, int u) {
-    const uint32_t dst = ring_base + buf * kStage;
+    const uint32_t dst = buf * kStage;
     const bool real = k0 < dv;
     if (u < UA) {
       uint32_t off;
@@ -360,9 +365,9 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
         ok = ok & ((a_mask[u] >> gk) & 1u) & (slot < cap32);
         off = a_base[u] + static_cast<uint32_t>((slot * ds + (k0 - gk * ds)) * 2);
       }
-      dma16(r_A, oob_unless(ok, off), dst + 1024u * (pw + NP * u));
+      copy(r_A, oob_unless(ok, off), dst + 1024u * (pw + NP * u));
     } else {
-      dma16(r_B, oob_unless(real, b_base[u - UA] + 2u * k0), dst + kStA + 1024u * (pw + NP * (u - UA)));
+      copy(r_B, oob_unless(real, b_base[u - UA] + 2u * k0), dst + kStA + 1024u * (pw + NP * (u - UA)));
     }
   };
   auto fill_ring = [&]() {
@@ -503,12 +508,16 @@ hipError_t launch_full(const FullParams& p, int mode, hipStream_t s) {
   const size_t rows = static_cast<size_t>(p.B) * p.T;
   const unsigned ncol = static_cast<unsigned>(p.dv / kBN);
   auto tiles = [&](int tbm) { return dim3(ncol * static_cast<unsigned>((rows + tbm - 1) / tbm)); };
+  const void* src = mode == 0 ? p.v : p.Vp;
+  const bool dma = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(p.Rm)) & 15) == 0;
   if (mode == 0) {
     hipLaunchKernelGGL(k_full_prep<true>, gprep, dim3(256), shm_pack, s, p);
-    hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
+    if (dma) hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0, false>), tiles(64), dim3(256), 0, s, p);
   } else {
     hipLaunchKernelGGL(k_full_prep<false>, gprep, dim3(256), shm_vals, s, p);
-    if (rows <= 1536) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
+    if (!dma) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0, false>), tiles(64), dim3(256), 0, s, p);
+    else if (rows <= 1536) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
     else hipLaunchKernelGGL((k_full_gemm<1, 256, 4, 3, 1, 4>), tiles(256), dim3(768), 0, s, p);
   }
   return hipGetLastError();

@@ -61,3 +61,32 @@ def test_full_products(H, S, B, T, keep, short):
         want = torch.where(full[b][:, None], zc, zc @ R64.T).reshape(T, H, 128).transpose(0, 1)
         d = (Vh[b].double() - want).abs()
         assert (d <= 2.0 ** -8 * want.abs() + dv ** 1.5 * 2.0 ** -24).all()
+
+
+def _off16(t):
+    """The same values at an address 8 bytes off a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+    out = buf[4:4 + t.numel()].view(t.shape)
+    out.copy_(t)
+    assert out.data_ptr() % 16 == 8
+    return out
+
+
+def test_full_products_off_16_byte_boundaries():
+    H, S, B, T = 8, 4, 2, 70
+    g = torch.Generator(device=DEV).manual_seed(5)
+    v = torch.randn((B, T, H, 128), generator=g, device=DEV).bfloat16()
+    R = (torch.randn((H * 128, H * 128), generator=g, device=DEV) * 0.03).bfloat16()
+    kept = torch.rand((B, T, S), generator=g, device=DEV) < 0.5
+    mask = (kept.long() << torch.arange(S, device=DEV)).sum(-1).to(torch.uint32)
+    Rt = rs.full_transpose(R)
+    out = lambda: (torch.zeros((B, T + 1), dtype=torch.int32, device=DEV),  # noqa: E731
+                   torch.zeros((B, T * S, H * 128 // S), dtype=torch.bfloat16, device=DEV))
+    off, Vp = rs.full_rotate_pack(v, Rt, mask, S, T * S, out=out())
+    Vh = rs.full_values(R, mask, off, Vp, S, H)
+    for a, b in ((_off16(v), Rt), (v, _off16(Rt))):
+        print("full products: operand 8 bytes off", flush=True)
+        off2, Vp2 = rs.full_rotate_pack(a, b, mask, S, T * S, out=out())
+        assert torch.equal(off2, off) and torch.equal(Vp2, Vp)
+    for a, b in ((_off16(R), Vp), (R, _off16(Vp))):
+        assert torch.equal(rs.full_values(a, mask, off, b, S, H), Vh)
