@@ -68,13 +68,8 @@ struct Flag {
 
 // Three waves per SIMD (three workgroups per CU): the register budget is
 // capped at 168 so that occupancy, not just the pipeline, hides latency.
-//
-// NG = 2 (few workgroups, long prefixes; not causal): two groups of four waves
-// take alternate tiles, each with its own tile buffers and softmax state, and the
-// first merges both at the end: half the chain of tiles where most CUs have no
-// workgroup. Every group must own a tile with keys (T > TK).
-template <int DH, int VM, int NG>
-__global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) void k_attend_bf16(AttendParams p) {
+template <int DH, int VM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_attend_bf16(AttendParams p) {
   // 32-token tiles at DH = 128 (shorter per-tile chains, 140 registers); 64 at
   // DH = 64 so that every thread has a value item per tile
   constexpr int TK = DH == 128 ? 32 : 64, MT = DH / 16, KS = DH / 32, KLD = DH + 8, ZLD = TK / 2 + 2;
@@ -90,19 +85,15 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
   // LDS at DH = 128: three workgroups per CU.
   constexpr int RBY = DH * 2, RCH = RBY / 16;  // bytes and 16-byte chunks per R_h row
   constexpr int RB = DH * RBY, KB = TK * KLD * 2, ZB = DH * ZLD * 4, SB = 4 * 16 * DH * 4;
-  constexpr int TB = KB + ZB, SMEM = RB + NG * TB > SB ? RB + NG * TB : SB;
-  constexpr int TS = NG * TK;  // tokens between a group's tiles
+  constexpr int SMEM = RB + KB + ZB > SB ? RB + KB + ZB : SB;
   static_assert(NKP >= 1 && NVI >= 1 && NHF >= 1, "tile shape");
   static_assert(RB % (4 * 1024) == 0, "R_h splits into whole 1 KB DMA blocks per wave");
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
   char* Rs = smem;
-  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  bf16* Ks = reinterpret_cast<bf16*>(smem + RB + grp * TB);
-  uint32_t* Zt = reinterpret_cast<uint32_t*>(smem + RB + grp * TB + KB);
-  __shared__ uint32_t sg_mask[NG][2][TK];
-  __shared__ int32_t sg_off[NG][2][TK];
-  auto& s_mask = sg_mask[grp];
-  auto& s_off = sg_off[grp];
+  bf16* Ks = reinterpret_cast<bf16*>(smem + RB);
+  uint32_t* Zt = reinterpret_cast<uint32_t*>(smem + RB + KB);
+  __shared__ uint32_t s_mask[2][TK];
+  __shared__ int32_t s_off[2][TK];
   int h, b;
   // 1D grid of (sample, head) items x query blocks. When B*H is a multiple of
   // 8 the query blocks of one item are consecutive workgroups of one XCD, so
@@ -122,7 +113,7 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
     xcd_split(item, p.H, h, b);
   }
   constexpr bool DENSE = VM == kDense;
-  const int tid = threadIdx.x & 255, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, g4 = lane >> 4;
   const int T = p.T, H = p.H, G = DENSE ? 1 : p.G, ds = DH / G;
   const uint32_t gm = group_mask(G);
   const int qq = qb * 64 + 16 * w + l16;
@@ -131,7 +122,7 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
 
   // R_h: wave w brings 1 KB blocks w*NRD .. w*NRD+NRD-1; lane i of a block
   // lands at byte 16i, which holds global chunk (16i % RBY)/16 ^ (row % RCH)
-  if (!DENSE && grp == 0) {
+  if constexpr (!DENSE) {
     constexpr int NRD = RB / 1024 / 4;
     const rsrc_t r_R = make_rsrc(static_cast<const bf16*>(p.R) + static_cast<size_t>(h) * DH * DH, RB);
     const uint32_t rbase = lds_addr(Rs);
@@ -282,13 +273,12 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
   // in the same order.
   uint32_t mA, mB;
   int32_t oA, oB;
-  const int tb = grp * TK;  // this group's first tile
-  load_k(kA, tb);
+  load_k(kA, 0);
   {
     uint32_t m0, m1;
     int32_t o0, o1;
-    load_meta(tb, m0, o0);
-    load_meta(tb + TS, m1, o1);
+    load_meta(0, m0, o0);
+    load_meta(TK, m1, o1);
     if (tid < TK) {
       s_mask[0][tid] = m0 & gm;
       s_off[0][tid] = o0;
@@ -303,11 +293,11 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
       qf[ks] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[ks]) ^ u32x4{0x80008000u, 0x80008000u,
                                                                                    0x80008000u, 0x80008000u});
   }
-  load_v(vA, tb, 0);
-  load_meta(tb + 2 * TS, mA, oA);
-  load_k(kB, tb + TS);
-  load_v(vB, tb + TS, 1);
-  load_meta(tb + 3 * TS, mB, oB);
+  load_v(vA, 0, 0);
+  load_meta(2 * TK, mA, oA);
+  load_k(kB, TK);
+  load_v(vB, TK, 1);
+  load_meta(3 * TK, mB, oB);
   // every wave has read slots 0 and 1 (tiles 0 and 1) before the first step
   // overwrites slot 0 with tile 2's metadata
   __syncthreads();
@@ -322,7 +312,7 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
     constexpr bool SPLIT = decltype(split)::value;
     if constexpr (SPLIT) store_k(kreg);
     else store_tile(kreg, vreg);
-    if (tid < TK) {  // masks/offsets of the group's tile after the next into this tile's slot
+    if (tid < TK) {  // masks/offsets of tile t0 + 2*TK into this tile's slot
       s_mask[slot][tid] = mreg & gm;
       s_off[slot][tid] = oreg;
     }
@@ -330,9 +320,9 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
     // operands two tiles ahead; past the end every load is out of range (no
     // memory access), so there is no branch here: a branch around the loads
     // makes the compiler wait on every outstanding load at its join
-    load_k(kreg, t0 + 2 * TS);
-    if constexpr (!SPLIT) load_v(vreg, t0 + 2 * TS, slot);
-    load_meta(t0 + 4 * TS, mreg, oreg);
+    load_k(kreg, t0 + 2 * TK);
+    if constexpr (!SPLIT) load_v(vreg, t0 + 2 * TK, slot);
+    load_meta(t0 + 4 * TK, mreg, oreg);
 
     // ---- S^T = K Q^T (rows: tile tokens 16*m2 + 4*g4 + i; column: this lane's query)
     f32x4 s[NM2];
@@ -375,29 +365,26 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
     mx = max_xor32(max_xor16(mx));
     const float m_cand = fmaxf(m_run, mx * sl2);  // sl2 >= 0
     if (__builtin_amdgcn_ballot_w64(m_cand > m_run + kSlack) != 0) {
-      float alpha = __builtin_amdgcn_exp2f(m_run - m_cand);  // 0 on the first tile
-      if (NG > 1) alpha = m_run == -INFINITY ? 0.f : alpha;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_cand);  // 0 on the first tile
 #pragma unroll
       for (int m = 0; m < MT; ++m) acc[m] *= alpha;
       l_run *= alpha;
       m_run = m_cand;
     }
-    // a group may see only scores of -inf where the other has finite ones
-    const float ref = NG > 1 && m_run == -INFINITY ? 0.f : m_run;
     float psum = 0.f;
     bf16x8 pb[NHF];
 #pragma unroll
     for (int m2 = 0; m2 < NM2; ++m2)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(s[m2][i], sl2, -ref));
+        const float pr = __builtin_amdgcn_exp2f(fmaf(s[m2][i], sl2, -m_run));
         psum += pr;
         pb[m2 >> 1][4 * (m2 & 1) + i] = static_cast<bf16>(pr);
       }
     l_run += psum;
     if constexpr (SPLIT) {
       store_v(vreg);
-      load_v(vreg, t0 + 2 * TS, slot);
+      load_v(vreg, t0 + 2 * TK, slot);
       __syncthreads();
     }
     // ---- O^T += Z~^T P^T, one MFMA per 32 tokens
@@ -422,30 +409,11 @@ __global__ __launch_bounds__(256 * NG) __attribute__((amdgpu_waves_per_eu(3))) v
   // prefix self-attention: keys past this block's last query are all masked
   const int t_stop = p.causal ? min(T, qb * 64 + 64) : T;
   // t_stop >= 1 (T >= 1): the first pair always runs, with no branch around it
-  step(Flag<true>{}, tb, 0, kA, vA, mA, oA);
-  step(Flag<false>{}, tb + TS, 1, kB, vB, mB, oB);
-  for (int t0 = 2 * TS; t0 < t_stop; t0 += 2 * TS) {
-    step(Flag<false>{}, t0 + tb, 0, kA, vA, mA, oA);
-    step(Flag<false>{}, t0 + tb + TS, 1, kB, vB, mB, oB);
-  }
-  if constexpr (NG == 2) {
-    // the second group's state through the tile buffers (free: the loop ended on a barrier)
-    static_assert(2 * TB >= 256 * (16 * MT + 8), "merge area");
-    f32x4* xa = reinterpret_cast<f32x4*>(smem + RB);
-    float* xm = reinterpret_cast<float*>(smem + RB + 256 * 16 * MT);
-    if (grp == 1) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m) xa[256 * m + tid] = acc[m];
-      xm[tid] = m_run;
-      xm[256 + tid] = l_run;
-    }
-    __syncthreads();
-    if (grp == 1) return;
-    const float m1 = xm[tid], mm = fmaxf(m_run, m1);
-    const float f0 = __builtin_amdgcn_exp2f(m_run - mm), f1 = __builtin_amdgcn_exp2f(m1 - mm);
-    l_run = l_run * f0 + xm[256 + tid] * f1;
-#pragma unroll
-    for (int m = 0; m < MT; ++m) acc[m] = acc[m] * f0 + xa[256 * m + tid] * f1;
+  step(Flag<true>{}, 0, 0, kA, vA, mA, oA);
+  step(Flag<false>{}, TK, 1, kB, vB, mB, oB);
+  for (int t0 = 2 * TK; t0 < t_stop; t0 += 2 * TK) {
+    step(Flag<false>{}, t0, 0, kA, vA, mA, oA);
+    step(Flag<false>{}, t0 + TK, 1, kB, vB, mB, oB);
   }
 
   // ---- R_h has landed (its DMA was issued before every other load; the loop
@@ -743,18 +711,12 @@ hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(p.B * p.H * ((p.Tq + 63) / 64)));
     const int ds = p.dh / p.G;
     const int vm = ds >= 8 ? kWide : (ds == 4 ? kDs4 : kDs2);
-    // Two groups per workgroup while every workgroup has a CU of its own and the
-    // chain of tiles is long enough to pay for the merge and the second group's
-    // start. One group and two, at most 256 workgroups: dh 128, T = 128 7.7 and
-    // 8.0 us, 177 9.4 and 10.4, 305 12.9 and 12.7, 600 21.3 and 17.0, 2048 63.1
-    // and 45.5; dh 64, T = 256 7.0 and 6.6, 561 13.8 and 13.0.
-    const int ng = !p.causal && grid.x <= 256 && p.T >= (p.dh == 128 ? 384 : 256) ? 2 : 1;
-#define ATT(DH, VM) (ng == 2 ? k_attend_bf16<DH, VM, 2> : k_attend_bf16<DH, VM, 1>)
-    auto k = p.dense ? (p.dh == 128 ? ATT(128, kDense) : ATT(64, kDense))
-             : p.dh == 128 ? (vm == kWide ? ATT(128, kWide) : vm == kDs4 ? ATT(128, kDs4) : ATT(128, kDs2))
-                           : (vm == kWide ? ATT(64, kWide) : vm == kDs4 ? ATT(64, kDs4) : ATT(64, kDs2));
-#undef ATT
-    hipLaunchKernelGGL(k, grid, dim3(256 * ng), 0, s, p);
+    auto k = p.dense ? (p.dh == 128 ? k_attend_bf16<128, kDense> : k_attend_bf16<64, kDense>)
+             : p.dh == 128 ? (vm == kWide ? k_attend_bf16<128, kWide> : vm == kDs4 ? k_attend_bf16<128, kDs4>
+                                                                                  : k_attend_bf16<128, kDs2>)
+                           : (vm == kWide ? k_attend_bf16<64, kWide> : vm == kDs4 ? k_attend_bf16<64, kDs4>
+                                                                                 : k_attend_bf16<64, kDs2>);
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   } else {
     const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * ((p.Tq + 15) / 16)));
     if (p.dh == 128) hipLaunchKernelGGL(k_attend_f32<128>, grid, dim3(256), 0, s, p);

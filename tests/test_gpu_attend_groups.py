@@ -1,6 +1,7 @@
-"""Attention with two groups of waves per workgroup (at most 256 workgroups,
-384 keys or more at dh = 128, 256 at dh = 64) against float64, at the edges of that rule and of the
-tiles, over packed groups of every load width and over plain values."""
+"""Attention over short and long prefixes, in few and many workgroups, against
+float64 at the edges of the tiles of keys (32 at dh = 128, 64 at dh = 64), over
+packed groups of every load width and over plain values, and the bits of a
+prefix against those it has in a batch."""
 import math
 
 import pytest
@@ -20,8 +21,8 @@ def test_attend_groups(dh, G, B, H, Tq, T):
     g = torch.Generator(device=DEV).manual_seed(T + dh + G)
     rn = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
     q, k, v = rn(B, Tq, H, dh), rn(B, T, H, dh), rn(B, T, H, dh)
-    q[:, :, 0] *= 8                       # peaked softmax: the two groups' maxima differ
-    # tokens of the second group's tiles out of reach: scores of -inf for queries above 0 there
+    q[:, :, 0] *= 8                       # peaked softmax: the tiles' maxima differ
+    # every other tile out of reach: scores of -inf for queries above 0 there
     tk = 32 if dh == 128 else 64
     hole = (torch.arange(T, device=DEV) // tk % 2) == 1
     q[0, :, 1, 0] = 1.0
@@ -48,3 +49,26 @@ def test_attend_groups(dh, G, B, H, Tq, T):
     # in norm, with head room for their largest values
     err = (got.double() - want).abs().max() / want.abs().max()
     assert err < 1e-2, err
+
+
+@pytest.mark.parametrize("dh,G,T", [(128, 8, 700), (128, 0, 700), (64, 16, 561), (64, 0, 300), (128, 32, 177)])
+def test_bits_do_not_depend_on_the_batch(dh, G, T):
+    """A prefix attended to in a large call has the bits it has by itself and
+    in a micro-batch."""
+    B, H, Tq = 40, 8, 5
+    g = torch.Generator(device=DEV).manual_seed(T + dh + G)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    q, k = rn(B, Tq, H, dh) * 2, rn(B, T, H, dh)
+    if G == 0:
+        V = rn(B, H, T, dh)
+        call = lambda b0, b1: rs.attend_values(q[b0:b1], k[b0:b1], V[b0:b1], out_dtype=torch.float32)  # noqa: E731
+    else:
+        R = torch.linalg.qr(torch.randn((H, dh, dh), generator=g, device=DEV))[0].bfloat16().contiguous()
+        mask = torch.randint(0, 2 ** G, (B, T), generator=g, device=DEV).to(torch.uint32)
+        off, Vp = rs.rotate_pack(rn(B, T, H, dh), R, mask, G, T * G)
+        call = lambda b0, b1: rs.attend(q[b0:b1], k[b0:b1], mask[b0:b1], off[b0:b1], Vp[b0:b1], R, G,  # noqa: E731
+                                        out_dtype=torch.float32)
+    print(f"attend batch independence dh={dh} G={G} T={T}", flush=True)
+    whole = call(0, B)
+    for b0, b1 in ((0, 1), (7, 9), (8, 40), (39, 40)):
+        assert torch.equal(call(b0, b1), whole[b0:b1]), (b0, b1)
