@@ -796,9 +796,8 @@ hipError_t launch_tile_t(const RouteParams& p, const Plan& q, size_t part_bytes,
     launch_pool_proj(p, sizeof(T) == 2, s);
     hipLaunchKernelGGL(k_route_fold<T>, dim3(nfold), dim3(256), 0, s, p, t);
   }
-  // tokens per launch: as many tiles as the partial products' area holds
-  const size_t per_tile = static_cast<size_t>(q.S) * q.MB * 16 * kTok * sizeof(float);
-  const size_t step = std::max<size_t>(1, std::min<size_t>(part_bytes / per_tile, size_t{1} << 20));
+  static_assert(16 * kTok * sizeof(float) == 4096, "partial products of a row block and tile");
+  const size_t step = route_tile_step(part_bytes, q.S, q.MB);
   for (size_t t0 = 0; t0 < q.tiles; t0 += step) {
     t.ntile = static_cast<int>(std::min(step, q.tiles - t0));
     t.tok0 = t0 * kTok;

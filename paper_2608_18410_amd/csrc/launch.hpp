@@ -15,11 +15,10 @@ struct RouteParams {
   float* cb;  // [B][Hr or G] per-sample language term (workspace)
   float* F;   // [Hr or G][C] folded role term (workspace)
   float* hbar;  // [B][d] pooled language state (workspace)
-  float* pcb;   // [ncb][B][Hr] partial language terms per column block (bf16 MLP2; workspace)
+  float* pcb;   // [ncb][B][route_ld(Hr or G)] language terms per column block (workspace)
   float* rpart;  // split-K router: both halves' partial products per 96-token tile, or null (workspace)
   int* rcnt;     // split-K router: finished halves per tile, zeroed by the pool kernel (workspace)
-  float* part;      // two-kernel form: partial products (workspace) and their bytes
-  size_t part_bytes;
+  float* part;   // two-kernel form: folded operands and partial products (workspace)
   int sk_polls;  // split-K router: polls the first half of a tile makes for the second (0: never shares)
   int mode;
   int k_by_type[4];
@@ -88,16 +87,26 @@ inline int route_tile_slices(int d, int MB, int kind, bool bf16) {
   const int s = route_tile_smax(MB, !bf16 ? kRouteSlicesF32 : kind == 0 ? 2 : kRouteSlicesBf16);
   return s < nch ? s : nch;
 }
-constexpr size_t kRouteTileArea = size_t{16} << 20;
+constexpr size_t kRouteTileArea = size_t{16} << 20;   // what a workspace holds for them at least, given the tokens
+constexpr size_t kRouteTileLaunch = size_t{1} << 30;  // what one launch fills of a larger area at most
+// Tiles of one launch, given the bytes for its partial products: as many as fit
+// them, one at least. The kernels address a launch's products by 32-bit offsets
+// within 2 GiB; the area of a workspace that also serves the split-K form (1152
+// bytes a token) passes that at 1.9 million tokens.
+inline size_t route_tile_step(size_t bytes, int S, int MB) {
+  const size_t n = (bytes < kRouteTileLaunch ? bytes : kRouteTileLaunch) / (static_cast<size_t>(S) * MB * 4096);
+  return n < 1 ? 1 : n;
+}
 // Operands of the finishing kernel in its own layout: F as matrix-core
 // fragments of whole 16 x 16 blocks, W2 in the lanes' order, padded biases.
 inline size_t route_fold_floats(int Hr, int G, int C, int kind) {
   const size_t nb = route_tile_blocks(Hr, G, 0, kind), rb = route_tile_blocks(C, C, 0, 0);
   return nb * rb * 256 + (kind == 0 ? nb * G * 16 : 0) + rb * 16 + nb * 16;
 }
-// bytes of folded operands and partial products: an upper bound that never falls as B or T grows
-// (a workspace sized for a batch serves every smaller one); calls with more
-// tokens run in several launches
+// Bytes of folded operands and partial products, enough for kRouteTileArea of
+// the latter; never falls as B or T grows (a workspace sized for a batch serves
+// every smaller one). Calls with more tokens than the area holds run in several
+// launches.
 inline size_t route_tile_bytes(int B, int T, int Hr, int G, int C, int kind) {
   const int MB = route_tile_blocks(Hr, G, C, kind);
   const size_t tiles = (static_cast<size_t>(B) * T + 63) / 64;

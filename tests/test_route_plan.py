@@ -1,0 +1,46 @@
+"""Sizes and rules that the router's launches are planned by, from the header
+they stand in (host only: compiled for the CPU)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2608_18410_amd", "csrc")
+SOURCE = r"""
+#include <algorithm>
+#include "launch.hpp"
+using namespace rolesub;
+extern "C" {
+// bytes that one launch of the two-kernel form addresses, in the larger of the
+// areas that a workspace holds behind its other pieces
+size_t launch_bytes(int B, int T, int d, int Hr, int G, int C, int kind, int bf16, size_t* area, size_t* ntile) {
+  const int MB = route_tile_blocks(Hr, G, C, kind), S = route_tile_slices(d, MB, kind, bf16);
+  const size_t sk = (route_sk_part_floats(B, T, Hr, kind) + route_sk_cnt_ints(B, T, Hr, kind)) * 4;
+  *area = std::max(sk, route_tile_bytes(B, T, Hr, G, C, kind)) - route_fold_floats(Hr, G, C, kind) * 4;
+  *ntile = std::min(route_tile_step(*area, S, MB), (static_cast<size_t>(B) * T + 63) / 64);
+  return *ntile * S * MB * 4096;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
+                    str(d / "plan.cpp"), "-o", str(d / "plan.so")], check=True)
+    lib = ctypes.CDLL(str(d / "plan.so"))
+    lib.launch_bytes.restype = ctypes.c_size_t
+    return lib
+
+
+@pytest.mark.parametrize("d,Hr,G,C,kind", [(256, 128, 8, 8, 0), (64, 128, 8, 17, 0), (4096, 128, 32, 64, 0), (64, 300, 8, 8, 0),
+                                           (8000, 4000, 32, 64, 0), (4096, 0, 32, 6, 1), (33, 0, 1, 1, 1)])
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_launches_stay_within_32_bit_offsets(plan, d, Hr, G, C, kind, bf16):
+    area, ntile = ctypes.c_size_t(), ctypes.c_size_t()
+    for B, T in ((1, 1), (2, 80), (64, 177), (1500, 177), (11000, 177), (24000, 177), (1, 1 << 20), (1 << 20, 2000)):
+        n = plan.launch_bytes(B, T, d, Hr, G, C, kind, bf16, ctypes.byref(area), ctypes.byref(ntile))
+        assert 1 <= ntile.value and n < 2 ** 31 and n <= area.value, (B, T, n, area.value)
