@@ -1244,7 +1244,7 @@ hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0) {
+  if (ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0 && route_sk_fits(p.B, p.T)) {
     const dim3 grid(static_cast<unsigned>(2 * route_sk_tiles(p.B, p.T)));
     if (p.G <= 8) hipLaunchKernelGGL(k_route_mlp2_sk<8>, grid, dim3(64 * kSkW), 0, s, p, ncb);
     else if (p.G <= 16) hipLaunchKernelGGL(k_route_mlp2_sk<16>, grid, dim3(64 * kSkW), 0, s, p, ncb);

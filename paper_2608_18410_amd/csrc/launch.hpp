@@ -59,6 +59,11 @@ inline size_t route_sk_tiles(int B, int T) { return (static_cast<size_t>(B) * T 
 inline size_t route_sk_part_floats(int B, int T, int Hr, int kind) {
   return kind == 0 && Hr == 128 ? route_sk_tiles(B, T) * 2 * kRouteSkTok * 144 : 0;
 }
+// Whether its kernel's 32-bit offsets reach all of its partial products (up to
+// 1.86 million tokens); larger calls run the single kernel, in the same bits.
+inline bool route_sk_fits(int B, int T) {
+  return route_sk_tiles(B, T) * 2 * kRouteSkTok * 144 * sizeof(float) < (size_t{1} << 31);
+}
 inline size_t route_sk_cnt_ints(int B, int T, int Hr, int kind) {
   return kind == 0 && Hr == 128 ? route_sk_tiles(B, T) : 0;
 }

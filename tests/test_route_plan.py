@@ -21,6 +21,7 @@ size_t launch_bytes(int B, int T, int d, int Hr, int G, int C, int kind, int bf1
   *ntile = std::min(route_tile_step(*area, S, MB), (static_cast<size_t>(B) * T + 63) / 64);
   return *ntile * S * MB * 4096;
 }
+bool sk_fits(int B, int T) { return route_sk_fits(B, T); }
 }
 """
 
@@ -33,6 +34,7 @@ def plan(tmp_path_factory):
                     str(d / "plan.cpp"), "-o", str(d / "plan.so")], check=True)
     lib = ctypes.CDLL(str(d / "plan.so"))
     lib.launch_bytes.restype = ctypes.c_size_t
+    lib.sk_fits.restype = ctypes.c_bool
     return lib
 
 
@@ -44,3 +46,9 @@ def test_launches_stay_within_32_bit_offsets(plan, d, Hr, G, C, kind, bf16):
     for B, T in ((1, 1), (2, 80), (64, 177), (1500, 177), (11000, 177), (24000, 177), (1, 1 << 20), (1 << 20, 2000)):
         n = plan.launch_bytes(B, T, d, Hr, G, C, kind, bf16, ctypes.byref(area), ctypes.byref(ntile))
         assert 1 <= ntile.value and n < 2 ** 31 and n <= area.value, (B, T, n, area.value)
+
+
+def test_split_k_only_where_its_offsets_reach(plan):
+    for B, T in ((1, 48), (64, 177), (10000, 177), (10531, 177), (10532, 177), (11000, 177), (24000, 177), (1 << 20, 1000)):
+        tiles = -(-B * T // 96)  # two halves of six waves, nine 16-byte products a lane
+        assert plan.sk_fits(B, T) == (tiles * 2 * 6 * 64 * 9 * 16 < 2 ** 31), (B, T)
