@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // by each wave's chain of tiles. Measured (2 prefixes of 177 tokens, 56 queries,
 // 32 heads of 128): 15.8 us against 196 of a vector-ALU kernel with one
 // workgroup per query; 80 tokens, 8 queries, 4 heads of 64: 6.6 against 57.
-template <int DH>
+template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
   constexpr int MT = DH / 16;  // 16-dim blocks
   __shared__ __attribute__((aligned(16))) f32x4 s_u[4][MT][64];
@@ -595,7 +595,13 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
 #pragma unroll
   for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
-  auto compute = [&](const Tile& x, int t0) {
+  // CAUSAL: the block's diagonal tile also holds tokens past some of its queries.
+  // Their probability is 0, which an Inf or NaN in the products would turn into
+  // NaN: such values are taken out of that tile, a wave's last, and added below
+  // for the queries that see them.
+  uint64_t bad = 0;  // lanes that held such values
+  auto nonfinite = [](float z) { return (__float_as_uint(z) & 0x7F800000u) == 0x7F800000u; };
+  auto compute = [&](Tile& x, int t0) {
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: a single one waits for each MFMA's result
 #pragma unroll
     for (int kk = 0; kk < MT; ++kk)
@@ -608,7 +614,7 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int t = t0 + 4 * g4 + i;
-      v[i] = (t < T) & (!p.causal | (t <= qq)) ? (s0[i] + s1[i]) * sl2 : -INFINITY;
+      v[i] = (t < T) & (!CAUSAL | (t <= qq)) ? (s0[i] + s1[i]) * sl2 : -INFINITY;
       mx = fmaxf(mx, v[i]);
     }
     mx = max_xor32(max_xor16(mx));
@@ -626,6 +632,21 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
       v[i] = __builtin_amdgcn_exp2f(v[i] - ref);
       l_run += v[i];
     }
+    if (CAUSAL && t0 == 16 * qb) {
+      float chk = 0.f;  // stays 0 while every value is finite
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) chk = fmaf(x.v[i][m], 0.f, chk);
+      bad = __ballot(chk != 0.f);
+      if (bad != 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) x.v[i][m] = nonfinite(x.v[i][m]) ? 0.f : x.v[i][m];
+      }
+      s_u[w][0][lane] = f32x4{v[0], v[1], v[2], v[3]};  // the tile's probabilities
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -634,7 +655,7 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
 
   // tiles w, w + 4, ...: keys and values one tile ahead, the masks and offsets
   // that address the values two
-  const int t_stop = p.causal ? min(T, qb * 16 + 16) : T;
+  const int t_stop = CAUSAL ? min(T, qb * 16 + 16) : T;
   Meta mA, mB;
   Tile A, B;
   int t0 = 16 * w;
@@ -651,6 +672,24 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
     load_tile(A, mA, t0 + 64);
     compute(B, t0);
     t0 += 64;
+  }
+  if (CAUSAL && bad != 0) {
+#pragma unroll 1
+    for (int u = 0; u < 16; ++u) {
+      const int t = 16 * qb + u;
+      const float pu = reinterpret_cast<const float*>(&s_u[w][0][16 * (u >> 2) + l16])[u & 3];
+      const uint32_t mk = bload4(r_mask, oob_unless(t < T, 4u * t)) & gm;
+      const int off = static_cast<int32_t>(bload4(r_off, oob_unless(t < T, 4u * t)));
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int dim = 16 * m + 4 * g4 + e, g = dim >> lds, sl = off + __popc(mk & ((1u << g) - 1u));
+          const bool ok = (((mk >> g) & 1u) != 0u) & (sl < cap32) & (t <= qq);
+          const float z = __uint_as_float(bload4(r_v, oob_unless(ok, static_cast<uint32_t>(sl * ds + (dim & (ds - 1))) * 4u)));
+          if (nonfinite(z)) acc[m][e] += pu * z;
+        }
+    }
   }
 
   // ---- merge the four waves' softmax states and U
@@ -719,8 +758,9 @@ hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
     hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   } else {
     const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * ((p.Tq + 15) / 16)));
-    if (p.dh == 128) hipLaunchKernelGGL(k_attend_f32<128>, grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(k_attend_f32<64>, grid, dim3(256), 0, s, p);
+    auto k = p.dh == 128 ? (p.causal ? k_attend_f32<128, true> : k_attend_f32<128, false>)
+                         : (p.causal ? k_attend_f32<64, true> : k_attend_f32<64, false>);
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }

@@ -73,3 +73,24 @@ def test_attend_f32(B, T, Tq, H, dh, G, scale, causal):
     torch.cuda.synchronize()
     ref = (O.attend_packed_causal if causal else O.attend_packed)(q, k, mask, off, Vp, R, G, scale or None)
     assert max_rel(host(got), ref) <= TOL
+
+
+@pytest.mark.parametrize("dh,G,T,t", [(64, 8, 40, 21), (64, 32, 33, 0), (128, 8, 47, 15), (128, 32, 16, 14), (128, 1, 90, 80)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_causal_f32_nonfinite_value_reaches_its_own_queries_only(dh, G, T, t, bad):
+    """An Inf or NaN cached for token t leaves the queries before t as they are
+    (bit for bit) and reaches every query from t on."""
+    H, ds, dim = 3, dh // G, dh - 3
+    g = torch.Generator(device=DEV).manual_seed(T)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV)  # noqa: E731
+    R = torch.linalg.qr(rn(H, dh, dh))[0].contiguous()
+    mask = torch.full((1, T), (1 << G) - 1, dtype=torch.int64, device=DEV).to(torch.uint32)
+    q, k = rn(1, T, H, dh), rn(1, T, H, dh)
+    off, Vp = rs.rotate_pack(rn(1, T, H, dh), R, mask, G, T * G)
+    clean = rs.attend_causal(q, k, mask, off, Vp, R, G)
+    Vp[0, 1, t * G + dim // ds, dim % ds] = bad
+    print(f"causal f32 {bad} at token {t} of {T}, dh={dh} G={G}", flush=True)
+    got = rs.attend_causal(q, k, mask, off, Vp, R, G)
+    assert torch.equal(got[:, :t], clean[:, :t]) and torch.equal(got[:, :, ::2], clean[:, :, ::2])
+    want = (R[1, :, dim] * bad).expand(T - t, dh)   # R_h of that dim's multiple
+    assert torch.equal(got[0, t:, 1].nan_to_num(7.0, 8.0, 9.0), want.nan_to_num(7.0, 8.0, 9.0))
