@@ -305,11 +305,11 @@ __global__ __launch_bounds__(256) void k_route_fold(RouteParams p, TileParams t)
 }
 
 // DMA: rows and row strides are multiples of 16 bytes, 16-byte aligned.
-// Otherwise the stage is filled element by element (one stage at a time).
+// Otherwise the stages are filled through registers.
 template <class T, int NRB, bool DMA, bool DEEP>
 __global__ __launch_bounds__(256) void k_route_tile(RouteParams p, TileParams t) {
   constexpr int STEP = DEEP ? 2 : 1;  // stages per barrier
-  constexpr int NB = DEEP ? 10 : NRB == 2 ? 4 : 5;
+  constexpr int NB = !DMA ? 2 : DEEP ? 10 : NRB == 2 ? 4 : 5;
   constexpr int kWB = NRB * 16 * 128, kStage = kWB + kTok * 128;
   constexpr int NL = 2 * NRB + kTok / 8;  // 1 KB wave-loads per stage
   constexpr int UMAX = (NL + 3) / 4, UMIN = NL / 4;
@@ -351,35 +351,36 @@ __global__ __launch_bounds__(256) void k_route_tile(RouteParams p, TileParams t)
   for (int m = 0; m < NRB; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int th = 16 * w + l16;
 
-  if constexpr (DMA) {
-    const rsrc_t r_h = make_rsrc(hbase, static_cast<uint32_t>(nvalid) * dB);
-    const rsrc_t r_w = make_rsrc(wmain, static_cast<uint32_t>(nmain) * Ws);
-    const rsrc_t r_r = make_rsrc(p.W_r, static_cast<uint32_t>(C) * dB);
-    const uint32_t ring_base = lds_addr(ring);
-    // Wave-load j = w + 4u < NL of a stage: row groups 8j.. for j < 2 NRB
-    // (both halves of a block, so one matrix each), then token rows. Lane i
-    // carries row 8j + i/8, LDS piece i%8, global piece (i%8) ^ swizzle.
-    const int ri = lane >> 3, piece = lane & 7;
-    uint32_t base_off[UMAX], pcol[UMAX];
+  const rsrc_t r_h = make_rsrc(hbase, static_cast<uint32_t>(nvalid) * dB);
+  const rsrc_t r_w = make_rsrc(wmain, static_cast<uint32_t>(nmain) * Ws);
+  const rsrc_t r_r = make_rsrc(p.W_r, static_cast<uint32_t>(C) * dB);
+  // Wave-load j = w + 4u < NL of a stage: row groups 8j.. for j < 2 NRB
+  // (both halves of a block, so one matrix each), then token rows. Lane i
+  // carries row 8j + i/8, LDS piece i%8, global piece (i%8) ^ swizzle.
+  const int ri = lane >> 3, piece = lane & 7;
+  uint32_t base_off[UMAX], pcol[UMAX];
 #pragma unroll
-    for (int u = 0; u < UMAX; ++u) {
-      const int j = w + 4 * u;
-      uint32_t off = kOOB;
-      int r = 8 * j + ri;
-      if (j < 2 * NRB) {
-        const int gr = r0 + r, rr = gr - 16 * t.nbm;
-        if (rr < 0) {
-          if (gr < nmain) off = static_cast<uint32_t>(gr) * Ws;
-        } else if (rr < C) {
-          off = static_cast<uint32_t>(rr) * dB;
-        }
-      } else {
-        r = 8 * (j - 2 * NRB) + ri;
-        if (r < nvalid) off = static_cast<uint32_t>(r) * dB;
+  for (int u = 0; u < UMAX; ++u) {
+    const int j = w + 4 * u;
+    uint32_t off = kOOB;
+    int r = 8 * j + ri;
+    if (j < 2 * NRB) {
+      const int gr = r0 + r, rr = gr - 16 * t.nbm;
+      if (rr < 0) {
+        if (gr < nmain) off = static_cast<uint32_t>(gr) * Ws;
+      } else if (rr < C) {
+        off = static_cast<uint32_t>(rr) * dB;
       }
-      base_off[u] = off;
-      pcol[u] = 16u * (piece ^ swz8(r));
+    } else {
+      r = 8 * (j - 2 * NRB) + ri;
+      if (r < nvalid) off = static_cast<uint32_t>(r) * dB;
     }
+    base_off[u] = off;
+    pcol[u] = 16u * (piece ^ swz8(r));
+  }
+
+  if constexpr (DMA) {
+    const uint32_t ring_base = lds_addr(ring);
     auto issue_one = [&](int i, int u) {
       const int j = w + 4 * u;
       if (u >= UMIN && j >= NL) return;  // the last load of the waves that have one fewer
@@ -426,42 +427,61 @@ __global__ __launch_bounds__(256) void k_route_tile(RouteParams p, TileParams t)
     }
     wait_vmcnt<0>();  // trailing dummy loads land before the LDS is released
   } else {
-    const T* h = reinterpret_cast<const T*>(hbase);
-    for (int c = c0; c < c1; ++c) {
-      for (int it = tid; it < (16 * NRB + kTok) * EPC; it += 256) {
-        const int r = it / EPC, e = it % EPC, k = c * EPC + e;
-        T v = fromf<T>(0.f);
-        int lr = r;  // row within its LDS part (weights, tokens)
-        if (r < 16 * NRB) {
-          const int gr = r0 + r, rr = gr - 16 * t.nbm;
-          if (k < d) {
-            if (rr < 0) {
-              if (gr < nmain)
-                v = *reinterpret_cast<const T*>(static_cast<const char*>(wmain) + static_cast<size_t>(gr) * Ws +
-                                                k * sizeof(T));
-            } else if (rr < C) {
-              v = static_cast<const T*>(p.W_r)[static_cast<size_t>(rr) * d + k];
-            }
-          }
-        } else {
-          lr = r - 16 * NRB;
-          if (k < d && lr < nvalid) v = h[static_cast<size_t>(lr) * d + k];
+    // 16 bytes a lane through registers, two stages ahead of their use; the piece
+    // that a row ends in element by element. Bound by the round trip of a stage's
+    // loads. Measured, whole calls at d = 1001, Hr = 128: 8 tokens 29 us, 16 x 177
+    // 46, against 61 and 92 with every element loaded by itself for the stage at
+    // hand, and 47 and 204 with one workgroup per token.
+    struct Stage {
+      u32x4 v[UMAX];
+    };
+    const bool tail = d % (16 / static_cast<int>(sizeof(T))) != 0;
+    auto load = [&](Stage& x, int c) {
+#pragma unroll
+      for (int u = 0; u < UMAX; ++u) {
+        const int j = w + 4 * u;
+        if (u >= UMIN && j >= NL) break;  // the last load of the waves that have one fewer
+        const uint32_t col = static_cast<uint32_t>(c) * 128u + pcol[u];
+        const uint32_t off = oob_unless((c < c1) & (col + 16u <= dB) & (base_off[u] != kOOB), base_off[u] + col);
+        const rsrc_t r = j >= 2 * NRB ? r_h : r0 + 8 * j < 16 * t.nbm ? r_w : r_r;
+        x.v[u] = bload16(r, off);
+        if (tail && c == nch - 1 && c < c1 && col < dB && col + 16u > dB && base_off[u] != kOOB) {
+          const char* src = (j >= 2 * NRB ? hbase : static_cast<const char*>(r0 + 8 * j < 16 * t.nbm ? wmain : p.W_r)) +
+                            base_off[u] + col;
+          T e[16 / sizeof(T)];
+#pragma unroll
+          for (uint32_t i = 0; i < 16 / sizeof(T); ++i)
+            e[i] = col + i * sizeof(T) < dB ? reinterpret_cast<const T*>(src)[i] : fromf<T>(0.f);
+          __builtin_memcpy(&x.v[u], e, 16);
         }
-        const int byte = e * static_cast<int>(sizeof(T));
-        char* dst = ring + (r < 16 * NRB ? 0 : kWB) + lr * 128 + 16 * ((byte >> 4) ^ swz8(lr)) + (byte & 15);
-        *reinterpret_cast<T*>(dst) = v;
       }
-      __syncthreads();
+    };
+    auto step = [&](Stage& x, int c) {
+      char* st = ring + ((c - c0) & 1) * kStage;
+#pragma unroll
+      for (int u = 0; u < UMAX; ++u) {
+        const int j = w + 4 * u;
+        if (u >= UMIN && j >= NL) break;
+        *reinterpret_cast<u32x4*>(st + 1024 * j + 16 * lane) = x.v[u];
+      }
+      load(x, c + 2);
+      __syncthreads();  // (two stages: the next step writes the other one)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const u32x4 hb = *reinterpret_cast<const u32x4*>(ring + kWB + th * 128 + 16 * ((4 * ks + g4) ^ swz8(th)));
+        const u32x4 hb = *reinterpret_cast<const u32x4*>(st + kWB + th * 128 + 16 * ((4 * ks + g4) ^ swz8(th)));
 #pragma unroll
         for (int m = 0; m < NRB; ++m) {
           const int r = 16 * m + l16;
-          acc[m] = mma<T>(*reinterpret_cast<const u32x4*>(ring + r * 128 + 16 * ((4 * ks + g4) ^ swz8(r))), hb, acc[m]);
+          acc[m] = mma<T>(*reinterpret_cast<const u32x4*>(st + r * 128 + 16 * ((4 * ks + g4) ^ swz8(r))), hb, acc[m]);
         }
       }
-      __syncthreads();
+    };
+    Stage xa, xb;
+    load(xa, c0);
+    load(xb, c0 + 1);
+    for (int c = c0; c < c1; c += 2) {
+      step(xa, c);
+      if (c + 1 < c1) step(xb, c + 1);
     }
   }
   f32x4* out = reinterpret_cast<f32x4*>(t.part) +

@@ -49,6 +49,11 @@ def _outs(B, T, G):
     ("bf16", "mlp2", 2, 33, 7, 640, 300, 16, 3, 16, 0),     # several row chunks
     ("bf16", "mlp2", 2, 33, 7, 100, 20, 7, 3, 6, 0),        # unaligned rows
     ("bf16", "mlp2", 2, 33, 7, 512, 128, 8, 8, 64, 1),      # unaligned hidden states
+    ("bf16", "mlp2", 2, 70, 9, 1001, 128, 8, 8, 64, 0),     # rows of a whole number of stages and nine columns
+    ("bf16", "mlp2", 1, 70, 9, 71, 33, 5, 17, 3, 3),        # rows that end in seven columns
+    ("bf16", "additive", 2, 100, 9, 131, 0, 16, 6, 0, 1),   # three columns
+    ("f32", "mlp2", 2, 60, 9, 1003, 128, 8, 8, 64, 1),      # float32: three columns
+    ("f32", "additive", 1, 70, 9, 33, 0, 17, 3, 0, 3),      # one column in a stage of its own
     ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 64, 0),   # past the two-kernel range: one-kernel forms
     ("bf16", "additive", 2, 120, 9, 4096, 0, 16, 6, 0, 0),
     ("bf16", "additive", 3, 40, 9, 520, 0, 32, 40, 0, 0),   # five row blocks
