@@ -1185,22 +1185,6 @@ __global__ __launch_bounds__(64 * kSkW) void k_route_mlp2_sk(RouteParams p, int 
 }
 }  // namespace
 
-namespace {
-// Tokens up to which the two-kernel form is the faster one where the
-// one-kernel forms apply: at d = 4096, G = 8, 48 language tokens of 177, 21.6
-// against 31.8 us (1 prefix), 27 against 33.2 (16 prefixes), even at about 24
-// prefixes, where its pooling blocks and tiles no longer fit the chip together;
-// at d = 1024 17.4 against 28.6 (5 prefixes of 561). Both give the same bits.
-constexpr size_t kTileMaxTok = 3072;
-}  // namespace
-
-bool route_uses_tiles(int B, int T, int d, int G, int C, int Hr, int kind, bool bf16) {
-  const size_t ntok = static_cast<size_t>(B) * T;
-  const bool mfma_ok = bf16 && kind == 0 && Hr == 128 && C >= 1 && C <= 16 && G <= 32 && d % kRtKc == 0 &&
-                       ntok < (1u << 30);
-  return !mfma_ok || ntok <= kTileMaxTok;
-}
-
 void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s) {
   const int vec = bf16 ? 8 : 4, ncb = (p.d + 64 * vec - 1) / (64 * vec);
   const int nout = p.kind == 0 ? p.Hr : p.G;
@@ -1216,32 +1200,21 @@ void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s) {
   }
 }
 
-// The one-kernel forms (bf16 MLP2, Hr = 128, many tokens).
+// The one-kernel forms (bf16 MLP2, Hr = 128, many tokens): what route_uses_tiles leaves to them.
 hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s) {
   const size_t ntok = static_cast<size_t>(p.B) * p.T;
   if (ntok == 0) return hipSuccess;
-  constexpr int vec = 8;
-  const int ncb = (p.d + 64 * vec - 1) / (64 * vec);
-  const bool pcb_ok = p.pcb && p.d_e % 8 == 0 &&
-                      static_cast<size_t>(p.Hr) * (2 * static_cast<size_t>(p.d) + p.d_e) * 2 < (1ull << 31) &&
-                      static_cast<size_t>(ncb) * p.B * p.Hr * 4 < (1ull << 31) &&
-                      ((reinterpret_cast<uintptr_t>(p.W1) | reinterpret_cast<uintptr_t>(p.E)) & 15) == 0;
+  const int ncb = (p.d + 511) / 512;
   // the MFMA router adds the partial language terms itself when a block of
   // its tokens spans at most two samples and there are at most 8 partials
-  const bool ps = pcb_ok && p.T >= kRtTok && ncb <= 8;
-  if (pcb_ok) {
-    const unsigned nfb = static_cast<unsigned>((p.Hr * p.C + 255) / 256);
-    if (p.d % (64 * vec) == 0)
-      hipLaunchKernelGGL((k_route_pool<rolesub::bf16, true>), dim3(static_cast<unsigned>(p.B * ncb) + nfb), dim3(256), 0,
-                         s, p);
-    else
-      launch_pool_any(p, s);
-    if (!ps)
-      hipLaunchKernelGGL(k_route_cbsum, dim3(static_cast<unsigned>((p.B * p.Hr + 255) / 256)), dim3(256), 0,
-                         s, p, ncb);
-  } else {
-    launch_pool_proj(p, true, s);
-  }
+  const bool ps = p.T >= kRtTok && ncb <= 8;
+  const unsigned nfb = static_cast<unsigned>((p.Hr * p.C + 255) / 256);
+  if (p.d % 512 == 0)
+    hipLaunchKernelGGL((k_route_pool<rolesub::bf16, true>), dim3(static_cast<unsigned>(p.B * ncb) + nfb), dim3(256), 0, s, p);
+  else
+    launch_pool_any(p, s);
+  if (!ps)
+    hipLaunchKernelGGL(k_route_cbsum, dim3(static_cast<unsigned>((p.B * p.Hr + 255) / 256)), dim3(256), 0, s, p, ncb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0 && route_sk_fits(p.B, p.T)) {

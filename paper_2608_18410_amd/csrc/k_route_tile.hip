@@ -3,7 +3,7 @@
 // size, then one small kernel per 16 tokens that adds the slices and finishes
 // the router. Takes every shape, both router kinds and both types; the
 // single-kernel and split-K forms (bf16 MLP2, Hr = 128) are faster only for
-// many tokens (see launch_route).
+// many tokens (see route_uses_tiles).
 #include <algorithm>
 
 #include "common.hpp"
@@ -494,10 +494,11 @@ __global__ __launch_bounds__(256) void k_route_tile(RouteParams p, TileParams t)
 // ---------------------------------------------------------------------------
 // Finish: one workgroup of eight waves per 16 tokens. Wave w owns the main row
 // blocks m = w, w + 8, ...; lane (token l16, quarter g4) holds rows 16m + 4g4 +
-// i, the layout of the products. Every sum runs in the order of the one-kernel
-// forms (the halves of the hidden size; shares, then the bias; F a
-// on the f32 matrix cores; W2 per row block, then over the blocks, then over
-// the lane quarters), so the two give the same bits. The ranking gives every
+// i, the layout of the products. Where the one-kernel forms take a call of more
+// tokens (route_uses_tiles), every sum runs in their order, so that both give the
+// same bits: the halves of the hidden size; the column blocks' shares of the
+// language term, then the bias; F a on the f32 matrix cores; W2 per row block,
+// then over the blocks, then over the lane quarters. The ranking gives every
 // (token, group) a thread. With one or two waves per SIMD it is bound by the
 // instructions of one wave, so every operand is a 16-byte load at one lane
 // offset plus a scalar one (F, W2 and the biases folded into that layout by the

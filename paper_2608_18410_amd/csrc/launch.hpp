@@ -126,8 +126,24 @@ void launch_pool_any(const RouteParams& p, hipStream_t s);
 // for any strides and alignment.
 void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s);
 
-// Whether a call runs in the two-kernel form (a function of shape and type only).
-bool route_uses_tiles(int B, int T, int d, int G, int C, int Hr, int kind, bool bf16);
+// Tokens up to which the two-kernel form is the faster one where the
+// one-kernel forms apply: at d = 4096, G = 8, 48 language tokens of 177, 21.6
+// against 31.8 us (1 prefix), 27 against 33.2 (16 prefixes), even at about 24
+// prefixes, where its pooling blocks and tiles no longer fit the chip together;
+// at d = 1024 17.4 against 28.6 (5 prefixes of 561). Both give the same bits.
+constexpr size_t kRouteTileMaxTok = 3072;
+// Whether a call runs in the two-kernel form (a function of shape, type and
+// alignment). The one-kernel forms take bf16 MLP2 routers of 128 units whose
+// operands are rows of whole 16-byte pieces from 16-byte boundaries, which is
+// what their LDS DMA copies, and language terms within 2 GiB.
+inline bool route_uses_tiles(const RouteParams& p, bool bf16) {
+  const size_t ntok = static_cast<size_t>(p.B) * p.T, ncb = (static_cast<size_t>(p.d) + 511) / 512;
+  const bool one = bf16 && p.kind == 0 && p.Hr == 128 && p.C >= 1 && p.C <= 16 && p.G <= 32 && p.d % 64 == 0 &&
+                   p.d_e % 8 == 0 && ntok < (size_t{1} << 30) && ncb * p.B * 128 * sizeof(float) < (size_t{1} << 31) &&
+                   ((reinterpret_cast<uintptr_t>(p.h) | reinterpret_cast<uintptr_t>(p.W1) |
+                     reinterpret_cast<uintptr_t>(p.W_r) | reinterpret_cast<uintptr_t>(p.E)) & 15) == 0;
+  return !one || ntok <= kRouteTileMaxTok;
+}
 hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s);
 hipError_t launch_select(const RouteParams& p, hipStream_t s);
 

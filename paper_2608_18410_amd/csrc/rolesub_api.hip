@@ -227,7 +227,7 @@ hipError_t run_tiles(RouteParams p, bool bf16, void* workspace, size_t bytes, hi
 // and the two-kernel form runs over ranges of samples that leave room for one.
 hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes, bool split, hipStream_t s) {
   const RouteWs w = route_ws(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind);
-  if (!route_uses_tiles(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind, bf16)) {
+  if (!route_uses_tiles(p, bf16)) {
     char* ws = static_cast<char*>(workspace);
     p.cb = reinterpret_cast<float*>(ws);
     p.F = reinterpret_cast<float*>(ws + w.off_F);

@@ -55,6 +55,8 @@ def _outs(B, T, G):
     ("f32", "mlp2", 2, 60, 9, 1003, 128, 8, 8, 64, 1),      # float32: three columns
     ("f32", "additive", 1, 70, 9, 33, 0, 17, 3, 0, 3),      # one column in a stage of its own
     ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 64, 0),   # past the two-kernel range: one-kernel forms
+    ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 64, 1),   # so many, unaligned hidden states
+    ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 4, 0),    # so many, unaligned rows of W1
     ("bf16", "additive", 2, 120, 9, 4096, 0, 16, 6, 0, 0),
     ("bf16", "additive", 3, 40, 9, 520, 0, 32, 40, 0, 0),   # five row blocks
     ("bf16", "additive", 1, 17, 0, 33, 0, 1, 1, 0, 0),      # one group, odd hidden size
@@ -141,3 +143,28 @@ def test_scores_do_not_depend_on_the_batch(B, n_vis, n_lang, d, G, C):
         for name in ("mask", "idx", "count", "scores"):
             assert torch.equal(a[name][b0:b1], b[name]) and torch.equal(n[name][b0:b1], b[name]), name
         assert torch.equal(pa[b0:b1], pb)
+
+
+@pytest.mark.parametrize("what,de", [("h", 64), ("W1", 64), ("W_r", 64), ("E", 64), ("", 4)])
+def test_scores_do_not_depend_on_the_batch_off_16_bytes(what, de):
+    """The same with one operand off 16-byte boundaries: every number of tokens
+    takes the form that loads it through registers."""
+    B, G, C, d = 40, 8, 8, 1024
+    w = synth.workload(2).replace(B=B, d=d, G=G, C=C, d_e=de, n_vis=100, n_lang=20, n_prop=0)
+
+    def put_off(a, shift):
+        return torch.empty(a.size + shift, dtype=torch.bfloat16, device=DEV)[shift:].view(a.shape).copy_(put(a, torch.bfloat16))
+
+    wt = _weights(w, "mlp2", np.random.default_rng(d))
+    router = rs.Router.mlp2(**{k: put_off(v, 3 if k == what else 0) for k, v in wt.items()})
+    h = put_off(synth.round_to(np.random.default_rng(1).standard_normal((B, w.T, d)), "bf16"), 1 if what == "h" else 0)
+    types = put_u8(np.broadcast_to(w.types(), (B, w.T)).copy())
+    budget = rs.make_budget(rs.TOPK, (G // 2, G // 2, G, G))
+    print(f"batch independence, {what or 'rows'} off 16 bytes, d_e={de}", flush=True)
+    a = rs.route(types, budget, G, h=h, router=router)
+    n = rs.route_noalloc(types, budget, G, h=h, router=router, out=_outs(B, w.T, G))
+    for b0, b1 in ((0, 9), (9, 30), (39, 40)):
+        b = rs.route(types[b0:b1], budget, G, h=h[b0:b1], router=router)
+        torch.cuda.synchronize()
+        for name in ("mask", "idx", "count", "scores"):
+            assert torch.equal(a[name][b0:b1], b[name]) and torch.equal(n[name][b0:b1], b[name]), name

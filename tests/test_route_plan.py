@@ -21,6 +21,14 @@ size_t launch_bytes(int B, int T, int d, int Hr, int G, int C, int kind, int bf1
   *ntile = std::min(route_tile_step(*area, S, MB), (static_cast<size_t>(B) * T + 63) / 64);
   return *ntile * S * MB * 4096;
 }
+// h, W1, W_r and E at the addresses given
+bool uses_tiles(int B, int T, int d, int G, int C, int d_e, int Hr, int kind, int bf16, size_t h, size_t W1, size_t W_r, size_t E) {
+  RouteParams p = {};
+  p.B = B; p.T = T; p.d = d; p.G = G; p.C = C; p.d_e = d_e; p.Hr = Hr; p.kind = kind;
+  p.h = reinterpret_cast<void*>(h); p.W1 = reinterpret_cast<void*>(W1);
+  p.W_r = reinterpret_cast<void*>(W_r); p.E = reinterpret_cast<void*>(E);
+  return route_uses_tiles(p, bf16);
+}
 bool sk_fits(int B, int T) { return route_sk_fits(B, T); }
 }
 """
@@ -34,7 +42,7 @@ def plan(tmp_path_factory):
                     str(d / "plan.cpp"), "-o", str(d / "plan.so")], check=True)
     lib = ctypes.CDLL(str(d / "plan.so"))
     lib.launch_bytes.restype = ctypes.c_size_t
-    lib.sk_fits.restype = ctypes.c_bool
+    lib.sk_fits.restype = lib.uses_tiles.restype = ctypes.c_bool
     return lib
 
 
@@ -52,3 +60,21 @@ def test_split_k_only_where_its_offsets_reach(plan):
     for B, T in ((1, 48), (64, 177), (10000, 177), (10531, 177), (10532, 177), (11000, 177), (24000, 177), (1 << 20, 1000)):
         tiles = -(-B * T // 96)  # two halves of six waves, nine 16-byte products a lane
         assert plan.sk_fits(B, T) == (tiles * 2 * 6 * 64 * 9 * 16 < 2 ** 31), (B, T)
+
+
+def test_one_kernel_forms_take_only_what_their_dma_copies(plan):
+    A = 0x7f0000001000  # 16-byte boundary
+
+    def tiles(B=64, T=177, d=4096, G=8, C=8, d_e=128, Hr=128, kind=0, bf16=1, off=(0, 0, 0, 0)):
+        return plan.uses_tiles(B, T, d, G, C, d_e, Hr, kind, bf16, *(ctypes.c_size_t(A + x) for x in off))
+
+    assert not tiles() and not tiles(B=1, T=3073) and not tiles(off=(16, 32, 48, 64)) and not tiles(d=64, d_e=8)
+    assert tiles(B=1, T=3072) and tiles(bf16=0) and tiles(kind=1) and tiles(Hr=64) and tiles(C=17) and tiles(d=4128)
+    assert tiles(d_e=4) and tiles(d_e=127)
+    for i in range(4):
+        for x in (2, 4, 8, 14):
+            off = [0] * 4
+            off[i] = x
+            assert tiles(off=off), off
+    # language terms of 2 GiB and more
+    assert tiles(B=1 << 22, T=2, d=64) and not tiles(B=(1 << 22) - 1, T=2, d=64)
