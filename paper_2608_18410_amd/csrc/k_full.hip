@@ -217,7 +217,8 @@ __global__ __launch_bounds__(256) void k_full_prep(FullParams p) {
 // fragment reads). One barrier per stage. NCP = 0: every wave issues its share of
 // the DMAs between its MFMAs. NCP > 0: NCP waves do nothing else, since a wave whose
 // DMA waits for the texture unit holds up the MFMAs behind it.
-// Operands off 16-byte boundaries (DMA = false) go through registers instead.
+// Operands off 16-byte boundaries (DMA = false) go through registers instead, two
+// stages in flight, and two LDS buffers (see the loop).
 // Bound by the texture unit, which takes a 128-byte line of a DMA in about 2.6
 // clocks, and for the 256-row tile by that and the MFMAs in turn (a wave that
 // only touches later lines to bring them into L2 made both slower, 52 -> 79 us).
@@ -231,6 +232,11 @@ __global__ __launch_bounds__(256) void k_full_prep(FullParams p) {
 //     copying waves: 87; 128 rows: 97-118; 64 rows: 121. One prefix (16), 64 rows:
 //     65 (70) -> 37 (41) us, 256 rows: 54 (57). A values product over each group's kept
 //     rows only, with f32 accumulators in LDS, took 140 us (uncoalesced fragments).
+//   Off 16-byte boundaries, 8 (2) bytes off, preparation included, against the
+//     register staging before the DMA rings: rotate 69.5 (68) -> 60 (73) us at 64
+//     prefixes, 44 (44) -> 36.5 (38) at one; values, 128 rows as there, 98 (101) -> 89
+//     (93) and 67 (67) -> 58 (59.5). Loaded and stored at once, nothing in flight: 147
+//     (151), 120 (122), 284 (288) and 119 (120).
 __device__ __forceinline__ int full_swz(int row) { return (row >> 1) & 7; }
 
 template <int MODE, int TBM, int WM, int RING, int NWG, int NCP, bool DMA = true>
@@ -238,7 +244,8 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
   constexpr int NW = 2 * WM, NT = 64 * NW, NP = NCP ? NCP : NW, MI = TBM / WM / 16;  // MFMA waves, their threads, copying waves, 16-row blocks per wave
   constexpr int kStA = TBM * kBK * 2, kStB = kBN * kBK * 2, kStage = kStA + kStB;  // bytes
   constexpr int UA = kStA / 1024 / NP, UB = kStB / 1024 / NP;  // A and B DMAs per copying wave and stage
-  static_assert(kBK == 64 && kStA % (1024 * NP) == 0 && kStB % (1024 * NP) == 0 && RING >= 3, "stage shape");
+  static_assert(kBK == 64 && kStA % (1024 * NP) == 0 && kStB % (1024 * NP) == 0 && (DMA ? RING >= 3 : RING == 2 && NCP == 0),
+                "stage shape");
   __shared__ __attribute__((aligned(16))) char ring[RING * kStage];
   __shared__ int pre[kFullMaxB + 1];
   __shared__ int r_b[TBM], r_t[TBM], r_off[TBM];
@@ -347,12 +354,8 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
   };
   int kq = tile_or == 0 ? dv : static_cast<int>(__builtin_ctz(tile_or)) * ds;
   const int nst = MODE == 0 ? dv / kBK : __popc(tile_or) * (ds / kBK);
-  auto copy = [&](rsrc_t r, uint32_t off, uint32_t to) {
-    if constexpr (DMA) dma16(r, off, ring_base + to);
-    else *reinterpret_cast<u32x4*>(ring + to + 16 * lane) = bload16(r, off);
-  };
-  auto issue = [&](int buf, int k0, int u) {
-    const uint32_t dst = buf * kStage;
+  // piece u (A pieces, then B) at k0: copied from, to (the wave's 1024 bytes at)
+  auto piece = [&](int k0, int u, auto&& copy) {
     const bool real = k0 < dv;
     if (u < UA) {
       uint32_t off;
@@ -365,10 +368,14 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
         ok = ok & ((a_mask[u] >> gk) & 1u) & (slot < cap32);
         off = a_base[u] + static_cast<uint32_t>((slot * ds + (k0 - gk * ds)) * 2);
       }
-      copy(r_A, oob_unless(ok, off), dst + 1024u * (pw + NP * u));
+      copy(r_A, oob_unless(ok, off), 1024u * (pw + NP * u));
     } else {
-      copy(r_B, oob_unless(real, b_base[u - UA] + 2u * k0), dst + kStA + 1024u * (pw + NP * (u - UA)));
+      copy(r_B, oob_unless(real, b_base[u - UA] + 2u * k0), kStA + 1024u * (pw + NP * (u - UA)));
     }
+  };
+  auto issue = [&](int buf, int k0, int u) {
+    const uint32_t dst = buf * kStage;
+    piece(k0, u, [&](rsrc_t r, uint32_t off, uint32_t to) { dma16(r, off, ring_base + (dst + to)); });
   };
   auto fill_ring = [&]() {
 #pragma unroll
@@ -396,7 +403,7 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
     __syncthreads();
     return;
   }
-  if (!NCP) fill_ring();
+  if (!NCP && DMA) fill_ring();
 
   f32x4 acc[MI][4];
 #pragma unroll
@@ -421,29 +428,73 @@ __global__ __launch_bounds__(128 * WM + 64 * NCP, (NWG * (2 * WM + NCP) + 3) / 4
     }
   };
   // A stage's two MFMA k-steps run one half stage behind their fragment reads.
-  // When every wave has read a stage's second half (the barrier in its middle),
-  // the DMAs of the stage RING further on refill its buffer, spread between MFMAs.
   Frags f0, f1;
-  __syncthreads();
-  read(f0, 0, 0);
-  int cur = 0;
-  for (int s = 0; s < nst; ++s) {
-    read(f1, cur, 1);
-#pragma unroll
-    for (int q = 0; q < 4 * MI; ++q) acc[q / 4][q % 4] = mfma_16x16x32(f0.a[q / 4], f0.b[q % 4], acc[q / 4][q % 4]);
-    if (!NCP) wait_vmcnt<(UA + UB) * (RING - 2)>();  // as a copying wave
+  if constexpr (DMA) {
+    // When every wave has read a stage's second half (the barrier in its middle),
+    // the DMAs of the stage RING further on refill its buffer, spread between MFMAs.
     __syncthreads();
-    const int nxt = cur + 1 == RING ? 0 : cur + 1;
-    read(f0, nxt, 0);
+    read(f0, 0, 0);
+    int cur = 0;
+    for (int s = 0; s < nst; ++s) {
+      read(f1, cur, 1);
 #pragma unroll
-    for (int q = 0; q < 4 * MI; ++q) {
-      acc[q / 4][q % 4] = mfma_16x16x32(f1.a[q / 4], f1.b[q % 4], acc[q / 4][q % 4]);
+      for (int q = 0; q < 4 * MI; ++q) acc[q / 4][q % 4] = mfma_16x16x32(f0.a[q / 4], f0.b[q % 4], acc[q / 4][q % 4]);
+      if (!NCP) wait_vmcnt<(UA + UB) * (RING - 2)>();  // as a copying wave
+      __syncthreads();
+      const int nxt = cur + 1 == RING ? 0 : cur + 1;
+      read(f0, nxt, 0);
 #pragma unroll
-      for (int u = 0; u < UA + UB; ++u)
-        if (!NCP && u * 4 * MI / (UA + UB) == q) issue(cur, kq, u);
+      for (int q = 0; q < 4 * MI; ++q) {
+        acc[q / 4][q % 4] = mfma_16x16x32(f1.a[q / 4], f1.b[q % 4], acc[q / 4][q % 4]);
+#pragma unroll
+        for (int u = 0; u < UA + UB; ++u)
+          if (!NCP && u * 4 * MI / (UA + UB) == q) issue(cur, kq, u);
+      }
+      if (!NCP) kq = next_k(kq);
+      cur = nxt;
     }
-    if (!NCP) kq = next_k(kq);
-    cur = nxt;
+  } else {
+    // Two register sets, each loaded two stages before it is stored, and two
+    // buffers: at the barrier in the middle of a stage the next one is in LDS and
+    // the one before it has been read. An even number of stages (ds is a multiple
+    // of 128).
+    struct Regs {
+      u32x4 v[UA + UB];
+    };
+    auto load = [&](Regs& x) {
+#pragma unroll
+      for (int u = 0; u < UA + UB; ++u) piece(kq, u, [&](rsrc_t r, uint32_t off, uint32_t) { x.v[u] = bload16(r, off); });
+      kq = next_k(kq);
+    };
+    auto store = [&](const Regs& x, int buf) {
+#pragma unroll
+      for (int u = 0; u < UA + UB; ++u) {
+        const int to = u < UA ? 1024 * (pw + NP * u) : kStA + 1024 * (pw + NP * (u - UA));
+        *reinterpret_cast<u32x4*>(ring + buf * kStage + to + 16 * lane) = x.v[u];
+      }
+    };
+    auto step = [&](Regs& x, int cur) {
+      read(f1, cur, 1);
+#pragma unroll
+      for (int q = 0; q < 4 * MI; ++q) acc[q / 4][q % 4] = mfma_16x16x32(f0.a[q / 4], f0.b[q % 4], acc[q / 4][q % 4]);
+      store(x, cur ^ 1);
+      load(x);
+      __syncthreads();
+      read(f0, cur ^ 1, 0);
+#pragma unroll
+      for (int q = 0; q < 4 * MI; ++q) acc[q / 4][q % 4] = mfma_16x16x32(f1.a[q / 4], f1.b[q % 4], acc[q / 4][q % 4]);
+    };
+    Regs ra, rb;
+    load(ra);
+    load(rb);
+    store(ra, 0);
+    load(ra);
+    __syncthreads();
+    read(f0, 0, 0);
+    for (int s = 0; s < nst; s += 2) {
+      step(rb, 0);
+      step(ra, 1);
+    }
   }
   wait_vmcnt<0>();  // as a copying wave
   __syncthreads();
@@ -513,10 +564,10 @@ hipError_t launch_full(const FullParams& p, int mode, hipStream_t s) {
   if (mode == 0) {
     hipLaunchKernelGGL(k_full_prep<true>, gprep, dim3(256), shm_pack, s, p);
     if (dma) hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 3, 2, 0, false>), tiles(64), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((k_full_gemm<0, 64, 2, 2, 2, 0, false>), tiles(64), dim3(256), 0, s, p);
   } else {
     hipLaunchKernelGGL(k_full_prep<false>, gprep, dim3(256), shm_vals, s, p);
-    if (!dma) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0, false>), tiles(64), dim3(256), 0, s, p);
+    if (!dma) hipLaunchKernelGGL((k_full_gemm<1, 128, 2, 2, 2, 0, false>), tiles(128), dim3(256), 0, s, p);
     else if (rows <= 1536) hipLaunchKernelGGL((k_full_gemm<1, 64, 2, 3, 2, 0>), tiles(64), dim3(256), 0, s, p);
     else hipLaunchKernelGGL((k_full_gemm<1, 256, 4, 3, 1, 4>), tiles(256), dim3(768), 0, s, p);
   }

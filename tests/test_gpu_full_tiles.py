@@ -63,12 +63,12 @@ def test_full_products(H, S, B, T, keep, short):
         assert (d <= 2.0 ** -8 * want.abs() + dv ** 1.5 * 2.0 ** -24).all()
 
 
-def _off16(t):
-    """The same values at an address 8 bytes off a 16-byte boundary."""
+def _off16(t, shift=4):
+    """The same values at an address 8 (or 2 shift) bytes off a 16-byte boundary."""
     buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
-    out = buf[4:4 + t.numel()].view(t.shape)
+    out = buf[shift:shift + t.numel()].view(t.shape)
     out.copy_(t)
-    assert out.data_ptr() % 16 == 8
+    assert out.data_ptr() % 16 == 2 * shift
     return out
 
 
@@ -89,4 +89,29 @@ def test_full_products_off_16_byte_boundaries():
         off2, Vp2 = rs.full_rotate_pack(a, b, mask, S, T * S, out=out())
         assert torch.equal(off2, off) and torch.equal(Vp2, Vp)
     for a, b in ((_off16(R), Vp), (R, _off16(Vp))):
+        assert torch.equal(rs.full_values(a, mask, off, b, S, H), Vh)
+
+
+@pytest.mark.parametrize("H,S,B,T,keep,short", [(1, 1, 1, 1, 0.5, False), (8, 1, 3, 43, 0.5, False), (8, 8, 2, 64, 0.4, True),
+                                                (32, 32, 5, 77, 0.1, False), (6, 6, 3, 129, 0.0, False)])
+@pytest.mark.parametrize("shift", [1, 4])
+def test_register_staging_gives_the_bits_of_the_dma(H, S, B, T, keep, short, shift):
+    """64-row rotation and 128-row values tiles staged through registers, at
+    their edges: partial last tiles, two stages in all, no stage at all."""
+    g = torch.Generator(device=DEV).manual_seed(10 * H + T)
+    v = torch.randn((B, T, H, 128), generator=g, device=DEV).bfloat16()
+    R = (torch.randn((H * 128, H * 128), generator=g, device=DEV) * 0.03).bfloat16()
+    kept = torch.rand((B, T, S), generator=g, device=DEV) < keep
+    mask = (kept.long() << torch.arange(S, device=DEV)).sum(-1).to(torch.uint32)
+    cap = max(1, int(kept.sum((1, 2)).max()) - 2) if short else T * S
+    Rt = rs.full_transpose(R)
+    out = lambda: (torch.zeros((B, T + 1), dtype=torch.int32, device=DEV),  # noqa: E731
+                   torch.zeros((B, cap, H * 128 // S), dtype=torch.bfloat16, device=DEV))
+    print(f"register staging H={H} S={S} B={B} T={T} cap={cap} shift={shift}", flush=True)
+    off, Vp = rs.full_rotate_pack(v, Rt, mask, S, cap, out=out())
+    Vh = rs.full_values(R, mask, off, Vp, S, H)
+    for a, b in ((_off16(v, shift), Rt), (v, _off16(Rt, shift))):
+        off2, Vp2 = rs.full_rotate_pack(a, b, mask, S, cap, out=out())
+        assert torch.equal(off2, off) and torch.equal(Vp2, Vp)
+    for a, b in ((_off16(R, shift), Vp), (R, _off16(Vp, shift))):
         assert torch.equal(rs.full_values(a, mask, off, b, S, H), Vh)
