@@ -22,11 +22,14 @@ __device__ __forceinline__ uint32_t score_key(float x) {
 // kept tokens are written in index order (block-wide scan of both flags).
 // Bound by the chain of steps, at any segment length that occurs: counting each
 // token's rank against every other grew with its square. Measured, 128 segments
-// of 256: 10.3 -> 7.1 us (the host's time for a call); 64 of 1400: 186 -> 13.4 us;
-// 4 of 8192: 5603 -> 59 us.
+// of 256: 8.9 -> 7.4 us; of 700: 51 -> 9.4; 64 of 1400: 186 -> 13.4; 4 of 8192:
+// 5603 -> 59. A short segment's ranks take less than the chain (128 segments of
+// 1, 16, 64, 128: 3.4, 3.6, 4.5, 5.9 us against 7.3), so up to kRankSeg tokens
+// are counted, one thread each.
 __global__ __launch_bounds__(256) void k_retain(RetainParams p) {
   constexpr int kReg = 4;  // keys per thread in registers; later ones are read from LDS
-  __shared__ uint32_t keys[kRetainMaxSeg];
+  constexpr int kRankSeg = 192;
+  __shared__ __attribute__((aligned(16))) uint32_t keys[kRetainMaxSeg];
   __shared__ int cnt[2][4][3];
   __shared__ int wgt[2][4], weq[2][4];
   const int b = blockIdx.x / p.n_seg, sg = blockIdx.x % p.n_seg;
@@ -34,6 +37,27 @@ __global__ __launch_bounds__(256) void k_retain(RetainParams p) {
   const int n = p.seg_len[sg], start = p.seg_start[sg], keep = p.seg_keep[sg];
   if (keep <= 0) return;
   const float* sc = p.scores + static_cast<size_t>(b) * p.N + start;
+  if (n <= kRankSeg) {
+    const uint32_t k = tid < n ? score_key(sc[tid]) : 0u;
+    keys[tid] = k;  // key 0 at an index past every token ranks before none
+    __syncthreads();
+    int rank = 0;
+    // four keys per 16-byte read; the same address in every lane is a broadcast
+#pragma unroll 4
+    for (int j = 0; j < n; j += 4) {
+      const u32x4 kj = *reinterpret_cast<const u32x4*>(keys + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rank += (kj[e] > k) | ((kj[e] == k) & (j + e < tid));
+    }
+    const bool kept = tid < n && rank < keep;
+    const uint64_t bal = __ballot(kept);
+    if (lane == 0) wgt[0][w] = __popcll(bal);
+    __syncthreads();
+    int at = __popcll(bal & ((1ull << lane) - 1ull));
+    for (int v = 0; v < w; ++v) at += wgt[0][v];
+    if (kept) p.keep_idx[static_cast<size_t>(b) * p.K + p.seg_out[sg] + at] = start + tid;
+    return;
+  }
   uint32_t kr[kReg];
 #pragma unroll
   for (int u = 0; u < kReg; ++u) {
@@ -66,7 +90,7 @@ __global__ __launch_bounds__(256) void k_retain(RetainParams p) {
     }
     t += up;
   }
-  // keys above t 
+  // keys above t
   {
     int c = 0;
 #pragma unroll

@@ -1,4 +1,4 @@
-"""Token retention at the edges of its chunks of 256 tokens and of the keys kept in
+"""Token retention at the edges of its two forms (192 tokens), its chunks of 256 tokens and of the keys kept in
 registers (1024), with ties, NaN, infinities, both zeros and denormals: the
 kept indices are those of a stable descending sort."""
 import numpy as np
@@ -10,7 +10,7 @@ import paper_2608_18410_amd as rs
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 3, 64, 255, 256, 257, 1023, 1024, 1025, 1400, 8192])
+@pytest.mark.parametrize("n", [1, 3, 64, 65, 191, 192, 193, 255, 256, 257, 1023, 1024, 1025, 1400, 8192])
 @pytest.mark.parametrize("kind", ["gauss", "ties", "special", "equal"])
 def test_retain_edges(n, kind):
     r = np.random.default_rng(n)
