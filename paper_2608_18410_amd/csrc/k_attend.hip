@@ -517,7 +517,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // by each wave's chain of tiles. Measured (2 prefixes of 177 tokens, 56 queries,
 // 32 heads of 128): 15.8 us against 196 of a vector-ALU kernel with one
 // workgroup per query; 80 tokens, 8 queries, 4 heads of 64: 6.6 against 57.
-template <int DH, bool CAUSAL>
+//
+// ONE: at most 64 keys, one tile per wave, where a second set of operands would
+// only cost occupancy (121 registers instead of 247 at dh = 128). Measured, one
+// query, 512 samples of 16 tokens, 8 heads of 128: 113 -> 53 us (48 with a
+// workgroup per query, which grows with the queries: 323 against 58 at 8); one
+// sample, 4 heads of 64: 5.8 -> 5.0 us.
+template <int DH, bool CAUSAL, bool ONE>
 __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
   constexpr int MT = DH / 16;  // 16-dim blocks
   __shared__ __attribute__((aligned(16))) f32x4 s_u[4][MT][64];
@@ -656,22 +662,30 @@ __global__ __launch_bounds__(256) void k_attend_f32(AttendParams p) {
   // tiles w, w + 4, ...: keys and values one tile ahead, the masks and offsets
   // that address the values two
   const int t_stop = CAUSAL ? min(T, qb * 16 + 16) : T;
-  Meta mA, mB;
-  Tile A, B;
   int t0 = 16 * w;
-  load_meta(mA, t0);
-  load_meta(mB, t0 + 64);
-  load_tile(A, mA, t0);
-  while (t0 < t_stop) {
-    load_meta(mA, t0 + 128);
-    load_tile(B, mB, t0 + 64);
-    compute(A, t0);
-    t0 += 64;
-    if (t0 >= t_stop) break;
-    load_meta(mB, t0 + 128);
-    load_tile(A, mA, t0 + 64);
-    compute(B, t0);
-    t0 += 64;
+  if constexpr (ONE) {
+    Meta mA;
+    Tile A;
+    load_meta(mA, t0);
+    load_tile(A, mA, t0);
+    if (t0 < t_stop) compute(A, t0);
+  } else {
+    Meta mA, mB;
+    Tile A, B;
+    load_meta(mA, t0);
+    load_meta(mB, t0 + 64);
+    load_tile(A, mA, t0);
+    while (t0 < t_stop) {
+      load_meta(mA, t0 + 128);
+      load_tile(B, mB, t0 + 64);
+      compute(A, t0);
+      t0 += 64;
+      if (t0 >= t_stop) break;
+      load_meta(mB, t0 + 128);
+      load_tile(A, mA, t0 + 64);
+      compute(B, t0);
+      t0 += 64;
+    }
   }
   if (CAUSAL && bad != 0) {
 #pragma unroll 1
@@ -758,8 +772,12 @@ hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
     hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   } else {
     const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * ((p.Tq + 15) / 16)));
-    auto k = p.dh == 128 ? (p.causal ? k_attend_f32<128, true> : k_attend_f32<128, false>)
-                         : (p.causal ? k_attend_f32<64, true> : k_attend_f32<64, false>);
+    const bool one = p.T <= 64;
+#define ATT(DH) \
+  (p.causal ? (one ? k_attend_f32<DH, true, true> : k_attend_f32<DH, true, false>) \
+            : (one ? k_attend_f32<DH, false, true> : k_attend_f32<DH, false, false>))
+    auto k = p.dh == 128 ? ATT(128) : ATT(64);
+#undef ATT
     hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();

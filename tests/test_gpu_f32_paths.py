@@ -57,7 +57,7 @@ def test_rotate_f32(B, T, H, dh, G):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,T,Tq,H,dh,G,scale", [(1, 1, 1, 1, 64, 8, 0.0), (1, 16, 17, 3, 64, 32, 0.0),
-                                                 (2, 63, 16, 4, 128, 4, 0.0), (3, 65, 33, 8, 128, 32, -0.3),
+                                                 (2, 63, 16, 4, 128, 4, 0.0), (2, 64, 17, 4, 64, 8, 0.0), (2, 64, 2, 8, 128, 16, 0.0), (3, 65, 33, 8, 128, 32, -0.3),
                                                  (1, 200, 5, 8, 128, 1, 0.5), (2, 129, 70, 5, 64, 2, 0.0)])
 def test_attend_f32(B, T, Tq, H, dh, G, scale, causal):
     Tq = T if causal else Tq
