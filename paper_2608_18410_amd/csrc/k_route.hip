@@ -1217,7 +1217,13 @@ hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s) {
     hipLaunchKernelGGL(k_route_cbsum, dim3(static_cast<unsigned>((p.B * p.Hr + 255) / 256)), dim3(256), 0, s, p, ncb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (ps && p.rpart && p.rcnt && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0 && route_sk_fits(p.B, p.T)) {
+  // Split-K where a half of the hidden size is long enough to pay for the exchange.
+  // Single and split, G = 8: d = 256, 64 x 177 tokens 19.8 and 23.2 us, 128 x 177
+  // 30.1 and 36.1; d = 512 20.9 and 24.1, 34.0 and 36.5; d = 768 23.7 and 25.7, 38.8 and
+  // 39.3 (18 x 177: 22.9 and 22.1); d = 896 25.5 and 25.8, 41.5 and 40.9; d = 1152 28.3
+  // and 27.3, 46.5 and 44.2; d = 3200 44.0 and 37.5, 82.7 and 69.9.
+  const bool split = ps && p.T >= kRouteSkMinT && p.d % (2 * kRtKc) == 0 && p.d > 768 && route_sk_fits(p.B, p.T);
+  if (split && p.rpart && p.rcnt) {
     const dim3 grid(static_cast<unsigned>(2 * route_sk_tiles(p.B, p.T)));
     if (p.G <= 8) hipLaunchKernelGGL(k_route_mlp2_sk<8>, grid, dim3(64 * kSkW), 0, s, p, ncb);
     else if (p.G <= 16) hipLaunchKernelGGL(k_route_mlp2_sk<16>, grid, dim3(64 * kSkW), 0, s, p, ncb);

@@ -119,7 +119,9 @@ def test_route_noalloc_ranges_of_samples():
 
 @pytest.mark.parametrize("B,n_vis,n_lang,d,G,C", [(20, 128, 48, 4096, 8, 8),   # split-K form
                                                   (40, 60, 21, 1024, 16, 6),   # split-K form, three samples a tile
-                                                  (16, 200, 48, 512, 32, 16),  # 32 groups
+                                                  (20, 128, 48, 896, 8, 8),    # split-K form, shortest hidden size
+                                                 (20, 128, 48, 640, 16, 8),   # single kernel, ragged column blocks
+                                                 (16, 200, 48, 512, 32, 16),  # 32 groups
                                                   (80, 30, 12, 768, 8, 5),     # short prefixes, ragged column blocks
                                                   (80, 30, 12, 64, 8, 1)])     # one stage of the hidden size
 def test_scores_do_not_depend_on_the_batch(B, n_vis, n_lang, d, G, C):
