@@ -1,7 +1,8 @@
 """The full-width products at the edges of their tiles: 64 rows per group in the
-rotation, 128 or 64 routed tokens (S above 16) per values tile with the kept
-rows of each group in blocks of 16, steps of 256 or 128 dims, and slots past
-the cache's capacity."""
+rotation; 64 or (more than 1536 tokens) 256 routed tokens per values tile, whose
+stages of 64 dims skip the groups that no row of the tile keeps; 64 and 128 rows
+staged through registers where an operand is off 16-byte boundaries; and slots
+past the cache's capacity."""
 import pytest
 import torch
 
@@ -12,15 +13,15 @@ DEV = "cuda"
 
 
 @pytest.mark.parametrize("H,S,B,T,keep", [
-    (1, 1, 1, 1, 0.5),      # one group of one head, one token
-    (8, 8, 1, 16, 0.5),     # steps of 128 dims, one block
-    (8, 4, 1, 63, 0.3),     # steps of 256, just under a rotation tile of rows
-    (6, 6, 3, 43, 0.7),     # one row past a values tile; group count not a multiple of 8
-    (24, 8, 2, 65, 0.4),    # groups of 384 dims: three steps of 128
+    (1, 1, 1, 1, 0.5),      # one group of one head, one token: two stages in all
+    (8, 8, 1, 16, 0.5),     # two stages per group, a quarter of a tile
+    (8, 4, 1, 63, 0.3),     # four stages per group, just under a tile of rows
+    (6, 6, 3, 43, 0.7),     # two rows past two values tiles; group count not a multiple of 8
+    (24, 8, 2, 65, 0.4),    # groups of 384 dims: six stages
     (8, 1, 2, 70, 0.5),     # one group: its routed tokens keep nothing
-    (16, 2, 2, 64, 0.5),    # groups of 1024 dims: four steps of 256
-    (32, 32, 2, 33, 0.06),  # the 64-row tile, most groups with under 16 rows
-    (32, 32, 1, 130, 0.9),  # the 64-row tile, nearly dense
+    (16, 2, 2, 64, 0.5),    # groups of 1024 dims, exactly two tiles of tokens
+    (32, 32, 2, 33, 0.06),  # most groups with a few rows
+    (32, 32, 1, 130, 0.9),  # nearly dense
 ])
 @pytest.mark.parametrize("short", [False, True])
 def test_full_products(H, S, B, T, keep, short):
@@ -61,6 +62,64 @@ def test_full_products(H, S, B, T, keep, short):
         want = torch.where(full[b][:, None], zc, zc @ R64.T).reshape(T, H, 128).transpose(0, 1)
         d = (Vh[b].double() - want).abs()
         assert (d <= 2.0 ** -8 * want.abs() + dv ** 1.5 * 2.0 ** -24).all()
+
+
+def _masks(B, T, S, routed, g, keep=0.5):
+    """Masks of B samples with routed[b] routed tokens anywhere (each keeping a
+    share of the groups, not all), the others keeping all."""
+    kept = torch.rand((B, T, S), generator=g, device=DEV) < keep
+    kept[..., 0] &= ~kept.all(-1)
+    for b in range(B):
+        order = torch.randperm(T, generator=g, device=DEV)
+        kept[b, order[routed[b]:]] = True
+    return kept, (kept.long() << torch.arange(S, device=DEV)).sum(-1).to(torch.uint32)
+
+
+@pytest.mark.parametrize("H,S,B,T,total,keep,short", [
+    (8, 8, 33, 65, 0, 0.5, False),       # no routed token: every tile returns
+    (8, 8, 33, 65, 1, 0.5, False),
+    (8, 8, 33, 65, 255, 0.5, False),     # a row short of a tile
+    (8, 8, 33, 65, 256, 0.5, False),
+    (8, 8, 33, 65, 257, 0.5, True),      # a tile of one row; slots past the capacity
+    (8, 1, 33, 65, 600, 0.5, False),     # one group: the routed tokens keep nothing, no stage runs
+    (8, 2, 25, 65, 900, 0.5, True),      # groups of 512 dims
+    (16, 16, 20, 81, 1500, 0.02, False),  # tiles whose rows keep few groups: most stages skipped
+    (6, 6, 300, 7, 2000, 0.9, False),    # many short samples, column tiles not a multiple of 8
+])
+def test_many_rows_match_single_samples_and_float64(H, S, B, T, total, keep, short):
+    """More than 1536 tokens: values in 256-row tiles with copying waves, bit for
+    bit what calls of one sample (64-row tiles) give, and within rounding of
+    float64."""
+    assert B * T > 1536
+    g = torch.Generator(device=DEV).manual_seed(total + S)
+    dv, ds = H * 128, H * 128 // S
+    r = torch.randperm(B * T, generator=g, device=DEV)[:total] // T
+    routed = torch.bincount(r, minlength=B).tolist()
+    kept, mask = _masks(B, T, S, routed, g, keep)
+    assert int((~kept.all(-1)).sum()) == total
+    v = torch.randn((B, T, H, 128), generator=g, device=DEV).bfloat16()
+    R = (torch.randn((dv, dv), generator=g, device=DEV) * dv ** -0.5).bfloat16()
+    Rt = rs.full_transpose(R)
+    cap = max(1, int(kept.sum((1, 2)).max()) - 2) if short else T * S
+    new = lambda n: (torch.zeros((n, T + 1), dtype=torch.int32, device=DEV),  # noqa: E731
+                     torch.zeros((n, cap, ds), dtype=torch.bfloat16, device=DEV))
+    print(f"full products H={H} S={S} B={B} T={T} routed={total} cap={cap}", flush=True)
+    off, Vp = rs.full_rotate_pack(v, Rt, mask, S, cap, out=new(B))
+    Vh = rs.full_values(R, mask, off, Vp, S, H)
+    full, R64 = kept.all(-1), R.double()
+    for b in range(B):
+        if b < 4 or b % 29 == 0:
+            o1, p1 = rs.full_rotate_pack(v[b:b + 1], Rt, mask[b:b + 1], S, cap, out=new(1))
+            assert torch.equal(o1[0], off[b]) and torch.equal(p1[0], Vp[b])
+            assert torch.equal(rs.full_values(R, mask[b:b + 1], o1, p1, S, H)[0], Vh[b]), b
+        # the cache as stored (slots past it read as zero), one rounding to bf16 and
+        # float32 sums of dv products
+        m = min(cap, int(off[b, -1]))
+        zc = torch.zeros((T * S, ds), dtype=torch.float64, device=DEV)
+        zc[kept[b].reshape(-1).nonzero()[:m, 0]] = Vp[b, :m].double()
+        zc = zc.reshape(T, dv)
+        want = torch.where(full[b][:, None], zc, zc @ R64.T).reshape(T, H, 128).transpose(0, 1)
+        assert ((Vh[b].double() - want).abs() <= 2.0 ** -8 * want.abs() + dv ** 1.5 * 2.0 ** -24).all(), b
 
 
 def _off16(t, shift=4):

@@ -55,7 +55,7 @@ def _bits(t):
 
 @pytest.mark.parametrize("noalloc", [False, True])
 def test_stack_layer_graph_replays(noalloc):
-    # route (split-K MLP2 router, or the allocation-free call) -> rotate+pack
+    # route (two-kernel MLP2 router, or the allocation-free call) -> rotate+pack
     # (offsets formed in the kernel) -> attend, 8 prefixes of the 7B stack
     w = synth.workload(4).replace(B=8)
     budget = rs.make_budget(w.mode, w.k_by_type, w.tau, w.kmin, w.kmax)
@@ -105,6 +105,57 @@ def test_stack_layer_graph_replays(noalloc):
         for b in range(w.B):
             assert torch.equal(vp_want[b].view(torch.int16), bufs.Vp[b, :, :int(n_slots[b])].view(torch.int16)), \
                 (rep, "Vp", b)
+
+
+@pytest.mark.parametrize("call", ["route", "noalloc", "allocate"])
+def test_many_token_route_graph_replays(call):
+    # more tokens than the two-kernel router takes: the split-K form with its tile
+    # tickets, or the single kernel (the allocation-free call)
+    B, T, d, G, C = 20, 177, 1024, 8, 8
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    n = lambda *s: (rn(*s).float() * s[-1] ** -0.5).bfloat16()  # noqa: E731
+    router = rs.Router.mlp2(n(C, d), n(C), rn(C, 64), n(128, 2 * d + 64), n(128), n(G, 128), n(G))
+    types = torch.zeros((B, T), dtype=torch.uint8, device=DEV)
+    types[:, 128:] = rs.LANG
+    h, h2, pri = rn(B, T, d), rn(B, T, d), rn(C)
+    budget = rs.make_budget(rs.TOPK, (4, 6, G, G))
+    u8 = lambda *s: torch.empty(s, dtype=torch.uint8, device=DEV)  # noqa: E731
+    out = dict(mask=torch.empty((B, T), dtype=torch.int32, device=DEV), idx=u8(B, T, G), count=u8(B, T),
+               scores=torch.empty((B, T, G), device=DEV))
+    if call == "allocate":
+        out.update(k=u8(B, T), priority=torch.empty((B, T), device=DEV))
+    size = rs.route_allocate_workspace_size if call == "allocate" else rs.route_workspace_size
+    ws = u8(size(B, T, G, d, router))
+
+    def run(x, o):
+        if call == "noalloc":
+            rs.route_noalloc(types, budget, G, h=x, router=router, out=o)
+        elif call == "allocate":
+            rs.route_allocate(types, (4, 6, G, G), G, x, router, pri, workspace=ws, out=o)
+        else:
+            rs.route(types, budget, G, h=x, router=router, workspace=ws, out=o)
+    other = {k: torch.empty_like(t) for k, t in out.items()}
+    _say(f"graph replays, {call} B={B} T={T}")
+    run(h, out)
+    torch.cuda.synchronize()
+    want = {k: _bits(t) for k, t in out.items()}
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        run(h, out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            run(h, out)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        run(h2, other)  # eager work on the same workspace between the replays
+        _sentinel(out.values())
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k, t in out.items():
+            assert torch.equal(want[k], _bits(t)), (rep, k)
 
 
 def test_full_width_layer_graph_replays():

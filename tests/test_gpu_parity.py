@@ -182,7 +182,7 @@ def test_rotate(cid, B, T, H, dh):
 # ----------------------------------------------------------------------------
 
 @pytest.mark.parametrize("cid,B,T,H,dh,G", [
-    (1, 1, 80, 4, 64, 8),        # f32 (vector kernel)
+    (1, 1, 80, 4, 64, 8),        # f32
     (2, 1, 305, 32, 128, 8),     # bf16, 16-dim groups, 7B layer shape
     (3, 3, 77, 8, 128, 8),       # ragged token count
     (5, 2, 301, 9, 128, 32),     # 4-dim groups, heads not a multiple of 8
@@ -245,7 +245,7 @@ def _attend_case(w, B, T, Tq, H, dh, G, counts=None, out_dtype=None, seed=0, sca
 
 
 @pytest.mark.parametrize("cid,B,T,Tq,H,dh,G", [
-    (1, 1, 80, 8, 4, 64, 8),           # tiny f32 (vector kernel)
+    (1, 1, 80, 8, 4, 64, 8),           # tiny f32
     (2, 1, 305, 56, 32, 128, 8),       # 7B layer shape (matrix cores)
     (3, 3, 113, 56, 32, 128, 8),
     (5, 2, 301, 70, 8, 128, 32),       # G=32 (4-dim groups), 2 query blocks, ragged T
@@ -287,7 +287,7 @@ def _attend_causal_case(w, B, T, H, dh, G, counts=None, out_dtype=None, seed=0, 
 
 
 @pytest.mark.parametrize("cid,B,T,H,dh,G", [
-    (1, 1, 80, 4, 64, 8),              # tiny f32 (vector kernel)
+    (1, 1, 80, 4, 64, 8),              # tiny f32
     (1, 2, 33, 4, 128, 4),             # f32, head dim 128
     (2, 1, 305, 32, 128, 8),           # 7B layer shape: 5 query blocks, ragged T
     (3, 3, 113, 8, 128, 8),
@@ -313,7 +313,7 @@ def test_attend_causal(cid, B, T, H, dh, G):
     (2, 2, 177, 56, 8, 128, 8, -0.0625),       # negative scale: scores of the opposite sign
     (5, 2, 90, 20, 4, 128, 32, -0.3),          # 4-dim groups
     (3, 2, 97, 20, 8, 64, 8, 0.5),             # head dim 64
-    (1, 1, 80, 8, 4, 64, 8, -0.2),             # f32 (vector kernel)
+    (1, 1, 80, 8, 4, 64, 8, -0.2),             # f32
 ])
 def test_attend_explicit_scale(cid, B, T, Tq, H, dh, G, scale):
     w = synth.workload(cid)
@@ -637,10 +637,8 @@ def test_route_mlp2(cid, B):
     _route_check(w, h, types, router_tensors(wt, tdtype(w)), ref, f"mlp2 workload {cid} B={B}")
 
 
-# bf16 MLP2 shapes that take the other launch paths: partial language terms
-# summed by their own kernel (short prefix: a router block spans more than two
-# samples; more than 8 column blocks; Hr = 64 on the generic router) and the
-# per-row projection (d not a multiple of 512).
+# bf16 MLP2 at short prefixes, more than 8 column blocks of the language term,
+# Hr = 64 and a hidden size that is no multiple of 512.
 @pytest.mark.parametrize("B,d,Hr,n_vis,n_lang", [(3, 1024, 128, 30, 9), (2, 4608, 128, 60, 9),
                                                  (2, 1024, 64, 80, 9), (2, 1088, 128, 80, 9)])
 def test_route_mlp2_launch_paths(B, d, Hr, n_vis, n_lang):
@@ -653,13 +651,12 @@ def test_route_mlp2_launch_paths(B, d, Hr, n_vis, n_lang):
     _route_check(w, h, types, router_tensors(wt, torch.bfloat16), ref, f"mlp2 B={B} d={d} Hr={Hr} T={w.T}")
 
 
-# The split-K router (two workgroups per 96-token tile, T >= 48, d a multiple
-# of 128) against the single kernel, which the no-alloc call runs: the same
-# bits for every token, including tiles that end inside a sample or past the
+# The call on a caller's workspace against the no-alloc call, bf16 MLP2: the
+# same bits for every token, including tiles that end inside a sample or past the
 # last token, tiles over three samples, 16 and 32 groups, and a second call on
-# the same workspace. With the default poll count the two halves of a tile
-# share its epilogue; with ROLESUB_SK_POLLS=0 the first to finish leaves the
-# tile to the other (unless it has already arrived).
+# the same workspace. At these numbers of tokens both run the two-kernel form;
+# the split-K and single kernels are compared in the same way at more tokens in
+# test_gpu_route_tiles.py.
 @pytest.mark.parametrize("polls", [None, "0"])
 @pytest.mark.parametrize("cid,B,n_vis,G", [(4, 3, 47, 8),      # T = 96: every tile is one whole sample
                                            (4, 2, 48, 8),      # T = 97: tiles straddle samples
@@ -683,7 +680,7 @@ def test_route_split_k_matches_single_kernel(cid, B, n_vis, G, polls, monkeypatc
                 "idx": torch.full((B, w.T, G), 7, dtype=torch.uint8, device=DEV),
                 "count": torch.full((B, w.T), 9, dtype=torch.uint8, device=DEV),
                 "scores": torch.full((B, w.T, G), float("nan"), dtype=torch.float32, device=DEV)}
-    _say(f"split-K router vs single kernel: B={B} T={w.T} G={G}")
+    _say(f"route vs route_noalloc: B={B} T={w.T} G={G}")
     a = rs.route(types, budget, G, h=h, router=router, workspace=ws, out=outs())
     a2 = rs.route(types, budget, G, h=h, router=router, workspace=ws, out=outs())
     b = rs.route_noalloc(types, budget, G, h=h, router=router, out=outs())

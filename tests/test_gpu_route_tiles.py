@@ -55,6 +55,7 @@ def _outs(B, T, G):
     ("f32", "mlp2", 2, 60, 9, 1003, 128, 8, 8, 64, 1),      # float32: three columns
     ("f32", "additive", 1, 70, 9, 33, 0, 17, 3, 0, 3),      # one column in a stage of its own
     ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 64, 0),   # past the two-kernel range: one-kernel forms
+    ("bf16", "mlp2", 20, 130, 30, 1024, 128, 16, 8, 64, 0),  # so many, split-K
     ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 64, 1),   # so many, unaligned hidden states
     ("bf16", "mlp2", 30, 130, 20, 512, 128, 8, 8, 4, 0),    # so many, unaligned rows of W1
     ("bf16", "additive", 2, 120, 9, 4096, 0, 16, 6, 0, 0),
@@ -170,3 +171,35 @@ def test_scores_do_not_depend_on_the_batch_off_16_bytes(what, de):
         torch.cuda.synchronize()
         for name in ("mask", "idx", "count", "scores"):
             assert torch.equal(a[name][b0:b1], b[name]) and torch.equal(n[name][b0:b1], b[name]), name
+
+
+@pytest.mark.parametrize("polls", [None, "0"])
+@pytest.mark.parametrize("B,T,G", [(33, 96, 8),     # every tile is one whole sample
+                                   (32, 97, 8),     # tiles straddle samples
+                                   (49, 64, 8),     # tiles over three samples
+                                   (38, 81, 16),    # the full-width prefix
+                                   (16, 200, 16),   # 16 groups, ragged last tile
+                                   (9, 349, 32)])   # 32 groups
+def test_split_k_matches_single_kernel_past_the_two_kernel_range(B, T, G, polls, monkeypatch):
+    """The split-K form (more than 3072 tokens, a hidden size above 768) against
+    the single kernel, which the allocation-free call runs: the same bits, also
+    on a second call on the same workspace, whether the halves of a tile share
+    its epilogue or the first leaves it to the other."""
+    if polls is not None:
+        monkeypatch.setenv("ROLESUB_SK_POLLS", polls)
+    d, C = 1024, 8
+    w = synth.workload(2).replace(B=B, d=d, G=G, C=C, d_e=64, n_vis=T - 20, n_lang=20, n_prop=0)
+    router = _router("mlp2", _weights(w, "mlp2", np.random.default_rng(T)), torch.bfloat16)
+    h = torch.randn((B, T, d), generator=torch.Generator(device=DEV).manual_seed(T), device=DEV).bfloat16()
+    types = put_u8(np.broadcast_to(w.types(), (B, T)).copy())
+    budget = rs.make_budget(rs.TOPK, (G // 2, G // 2, G, G))
+    ws = torch.empty(rs.route_workspace_size(B, T, G, d, router), dtype=torch.uint8, device=DEV)
+    print(f"split-K router vs single kernel: B={B} T={T} G={G} polls={polls}", flush=True)
+    a = rs.route(types, budget, G, h=h, router=router, workspace=ws, out=_outs(B, T, G))
+    a2 = rs.route(types, budget, G, h=h, router=router, workspace=ws, out=_outs(B, T, G))
+    b = rs.route_noalloc(types, budget, G, h=h, router=router, out=_outs(B, T, G))
+    torch.cuda.synchronize()
+    for r in (a2, b):
+        for name in ("mask", "idx", "count", "scores"):
+            assert torch.equal(r[name], a[name]), name
+    assert bool(torch.isfinite(a["scores"]).all())
