@@ -194,11 +194,18 @@ def _need_workspace(t):
         _need("workspace", t, (None,), torch.uint8)
 
 
+# torch.cuda.current_stream().cuda_stream without the Stream object, where this
+# torch has the two calls it takes
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    if stream is None:
-        # torch.cuda.current_stream().cuda_stream without the Stream object
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def make_budget(mode=TOPK, k_by_type=(0, 0, 0, 0), tau=0.0, kmin=0, kmax=0) -> Budget:

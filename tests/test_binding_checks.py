@@ -156,3 +156,19 @@ def test_micro_batches_and_buffer_rows():
     assert v.mask.shape == (3, 7) and v.offsets.shape == (3, 8) and v.Vp.shape == (3, 2, 9, 16)
     assert v.out.shape == (3, 3, 2, 64) and v.workspace is ws and v.z.numel() == 0
     assert v.mask.data_ptr() == bufs.mask[1].data_ptr() and v.Vp.is_contiguous()
+
+
+def test_stream_handle_without_the_private_calls(monkeypatch):
+    """A torch without the raw-stream calls falls back to the public ones."""
+    from types import SimpleNamespace
+
+    from paper_2608_18410_amd import rolesub
+    assert rolesub._stream(SimpleNamespace(cuda_stream=11)) == 11
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=7))
+    for name in ("_raw_stream", "_raw_device"):
+        with monkeypatch.context() as m:
+            m.setattr(rolesub, name, None)
+            assert rolesub._stream() == 7
+    monkeypatch.setattr(rolesub, "_raw_stream", lambda dev: 100 + dev)
+    monkeypatch.setattr(rolesub, "_raw_device", lambda: 3)
+    assert rolesub._stream() == 103
