@@ -227,6 +227,9 @@ rolesub_status rolesub_rotate_pack(const rolesub_dims* dims, rolesub_dtype dtype
  *   out [B,Tq,H,dh] in out_dtype (f32 or the call's dtype).
  * Packed slots >= cap_groups read as zero. workspace: at least
  * rolesub_attend_workspace_size() bytes (0 for the current kernels).
+ * A sample's outputs have the same bits in a call of any other samples.
+ * Scores are taken to be finite: with bf16 a query whose first tile of keys (32
+ * at dh = 128, 64 at dh = 64) scores -inf throughout gives NaN.
  * ------------------------------------------------------------------------ */
 size_t rolesub_attend_workspace_size(const rolesub_dims* dims, int32_t Tq);
 rolesub_status rolesub_attend(const rolesub_dims* dims, rolesub_dtype dtype, int32_t Tq,
@@ -247,6 +250,8 @@ rolesub_status rolesub_attend(const rolesub_dims* dims, rolesub_dtype dtype, int
  *   offsets, Vp, cap_groups, R, scale, workspace and errors as for
  *   rolesub_attend; out [B,T,H,dh] in out_dtype (f32 or the call's dtype).
  * T = 0 or B = 0 does nothing and returns OK.
+ * With bf16 an Inf or NaN among the values of token i gives NaN for the queries
+ * of the same aligned block of 64 before i too; with f32 only for those from i on.
  * ------------------------------------------------------------------------ */
 rolesub_status rolesub_attend_causal(const rolesub_dims* dims, rolesub_dtype dtype, const void* q,
                                      const void* k, const uint32_t* mask, const int32_t* offsets,
