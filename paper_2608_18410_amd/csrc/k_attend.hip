@@ -7,6 +7,8 @@
 //
 // Back-rotation is linear, so applying R_h after the weighted sum equals
 // summing the back-rotated routed values v~_i.
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -771,14 +773,28 @@ hipError_t launch_attend(const AttendParams& p, bool bf16, hipStream_t s) {
                                                                                  : k_attend_bf16<64, kDs2>);
     hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
   } else {
-    const dim3 grid(static_cast<unsigned>(static_cast<size_t>(p.B) * p.H * ((p.Tq + 15) / 16)));
     const bool one = p.T <= 64;
 #define ATT(DH) \
   (p.causal ? (one ? k_attend_f32<DH, true, true> : k_attend_f32<DH, true, false>) \
             : (one ? k_attend_f32<DH, false, true> : k_attend_f32<DH, false, false>))
     auto k = p.dh == 128 ? ATT(128) : ATT(64);
 #undef ATT
-    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p);
+    // a launch holds fewer than 2^32 threads: samples beyond that go to further ones
+    const size_t per = static_cast<size_t>(p.H) * ((p.Tq + 15) / 16);
+    const int step = static_cast<int>(std::min<size_t>(p.B, std::max<size_t>(1, ((size_t{1} << 24) - 1) / per)));
+    for (int b0 = 0; b0 < p.B; b0 += step) {
+      AttendParams r = p;
+      const size_t b = b0, row = static_cast<size_t>(p.H) * p.dh;
+      r.B = std::min(step, p.B - b0);
+      r.q = static_cast<const float*>(p.q) + b * p.Tq * row;
+      r.k = static_cast<const float*>(p.k) + b * p.T * row;
+      r.mask = p.mask + b * p.T;
+      r.offsets = p.offsets + b * (p.T + 1);
+      r.Vp = static_cast<const float*>(p.Vp) + b * p.H * p.cap * (p.dh / p.G);
+      r.out = static_cast<float*>(p.out) + b * p.Tq * row;
+      hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(r.B * per)), dim3(256), 0, s, r);
+      if (p.B - b0 <= step) break;  // (b0 + step may pass the largest int)
+    }
   }
   return hipGetLastError();
 }

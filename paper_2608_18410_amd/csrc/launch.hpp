@@ -130,7 +130,9 @@ void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s);
 // one-kernel forms apply: at d = 4096, G = 8, 48 language tokens of 177, 21.6
 // against 31.8 us (1 prefix), 27 against 33.2 (16 prefixes), even at about 24
 // prefixes, where its pooling blocks and tiles no longer fit the chip together;
-// at d = 1024 17.4 against 28.6 (5 prefixes of 561). Both give the same bits.
+// at d = 1024 17.4 against 28.6 (5 prefixes of 561). The line is d = 4096's, drawn
+// below the crossing; at smaller d the two-kernel form is still ahead there (17
+// prefixes, d = 1024: 16.7 and 22.3). Both give the same bits.
 constexpr size_t kRouteTileMaxTok = 3072;
 // Whether a call runs in the two-kernel form (a function of shape, type and
 // alignment). The one-kernel forms take bf16 MLP2 routers of 128 units whose
