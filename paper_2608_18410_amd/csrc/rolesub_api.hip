@@ -223,8 +223,9 @@ hipError_t run_tiles(RouteParams p, bool bf16, void* workspace, size_t bytes, hi
 
 // Router and selection of p's call in `workspace`. split: it holds
 // route_ws_bytes(); otherwise it is the no-alloc call's array, whose acceptance
-// has been checked: the single-kernel router needs no area of partial products,
-// and the two-kernel form runs over ranges of samples that leave room for one.
+// has been checked: the single-kernel router needs no area of partial products.
+// The two-kernel form runs over ranges of samples that a launch holds and that
+// leave room for partial products.
 hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes, bool split, hipStream_t s) {
   const RouteWs w = route_ws(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind);
   if (!route_uses_tiles(p, bf16)) {
@@ -238,25 +239,31 @@ hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes,
     p.sk_polls = route_sk_polls();
     return launch_route(p, bf16, s);
   }
-  if (split) return run_tiles(p, bf16, workspace, w.end, s);
-  // room for the folded operands and the partial products of one tile at least
-  // (2.2 MiB hold those of any router, see route_tile_smax; with one sample
-  // everything takes less than 7.5 MiB, since d + 2 Hr <= 16384)
-  const size_t room = route_fold_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float) + (size_t{9} << 18);
-  int nb = p.B;
-  while (nb > 1 && route_ws(nb, p.T, p.d, p.G, p.C, p.Hr, p.kind).off_s + room > ws_bytes) nb = (nb + 1) / 2;
+  // A launch holds fewer than 2^24 workgroups of 256 threads (HIP drops the rest
+  // without an error): pooling blocks and language-term rows of half of that.
+  const int per = std::max((p.d + 255) / 256, ((p.kind == 0 ? p.Hr : p.G) + 7) / 8);
+  int nb = std::min(p.B, std::max(1, (1 << 23) / per));
+  if (!split) {
+    // room for the folded operands and the partial products of one tile at least
+    // (2.2 MiB hold those of any router, see route_tile_smax; with one sample
+    // everything takes less than 7.5 MiB, since d + 2 Hr <= 16384)
+    const size_t room = route_fold_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float) + (size_t{9} << 18);
+    while (nb > 1 && route_ws(nb, p.T, p.d, p.G, p.C, p.Hr, p.kind).off_s + room > ws_bytes) nb = (nb + 1) / 2;
+  }
   const size_t es = bf16 ? 2 : 4, T = static_cast<size_t>(p.T);
-  for (int b0 = 0; b0 < p.B; b0 += nb) {
+  size_t b0 = 0;
+  for (int left = p.B; left > 0; b0 += nb, left -= nb) {
     RouteParams q = p;
     const size_t t0 = b0 * T;
-    q.B = std::min(nb, p.B - b0);
+    q.B = std::min(nb, left);
     q.h = static_cast<const char*>(p.h) + t0 * p.d * es;
     q.types = p.types + t0;
     if (p.scores_out) q.scores_out = p.scores_out + t0 * p.G;
+    if (p.priority) q.priority = p.priority + t0;
     if (p.mask) q.mask = p.mask + t0;
     if (p.idx) q.idx = p.idx + t0 * p.G;
     if (p.count) q.count = p.count + t0;
-    const hipError_t e = run_tiles(q, bf16, workspace, ws_bytes, s);
+    const hipError_t e = run_tiles(q, bf16, workspace, split ? w.end : ws_bytes, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
