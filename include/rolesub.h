@@ -154,9 +154,10 @@ rolesub_status rolesub_route(const rolesub_dims* dims, rolesub_dtype dtype,
  * callers that cannot allocate device memory (code under stream capture,
  * serving loops that forbid allocation). Same arguments as rolesub_route and
  * the same results, bit for bit (where rolesub_route uses the split-K form of
- * the bf16 MLP2 router this call runs its single kernel, which sums the same
- * terms in the same order; elsewhere both run the same kernels, this call over
- * ranges of samples where the array asks for it); the route workspace is a file-scope device array of
+ * the bf16 MLP2 router, or products the array has no room for, this call runs
+ * its single kernel, which sums the same terms in the same order; elsewhere both
+ * run the same kernels, this call over ranges of samples where the array asks
+ * for it); the route workspace is a file-scope device array of
  * ROLESUB_ROUTE_NOALLOC_MAX_BYTES that each device holds until the process
  * ends (its address is looked up once per device, with that device current).
  * Nothing is allocated or freed, by the library or any routine it calls.

@@ -134,17 +134,20 @@ void launch_pool_proj(const RouteParams& p, bool bf16, hipStream_t s);
 // below the crossing; at smaller d the two-kernel form is still ahead there (17
 // prefixes, d = 1024: 16.7 and 22.3). Both give the same bits.
 constexpr size_t kRouteTileMaxTok = 3072;
-// Whether a call runs in the two-kernel form (a function of shape, type and
-// alignment). The one-kernel forms take bf16 MLP2 routers of 128 units whose
-// operands are rows of whole 16-byte pieces from 16-byte boundaries, which is
-// what their LDS DMA copies, and language terms within 2 GiB.
-inline bool route_uses_tiles(const RouteParams& p, bool bf16) {
+// Whether the one-kernel forms can take a call (a function of shape, type and
+// alignment): bf16 MLP2 routers of 128 units whose operands are rows of whole
+// 16-byte pieces from 16-byte boundaries, which is what their LDS DMA copies, and
+// language terms within 2 GiB.
+inline bool route_one_kernel_ok(const RouteParams& p, bool bf16) {
   const size_t ntok = static_cast<size_t>(p.B) * p.T, ncb = (static_cast<size_t>(p.d) + 511) / 512;
-  const bool one = bf16 && p.kind == 0 && p.Hr == 128 && p.C >= 1 && p.C <= 16 && p.G <= 32 && p.d % 64 == 0 &&
-                   p.d_e % 8 == 0 && ntok < (size_t{1} << 30) && ncb * p.B * 128 * sizeof(float) < (size_t{1} << 31) &&
-                   ((reinterpret_cast<uintptr_t>(p.h) | reinterpret_cast<uintptr_t>(p.W1) |
-                     reinterpret_cast<uintptr_t>(p.W_r) | reinterpret_cast<uintptr_t>(p.E)) & 15) == 0;
-  return !one || ntok <= kRouteTileMaxTok;
+  return bf16 && p.kind == 0 && p.Hr == 128 && p.C >= 1 && p.C <= 16 && p.G <= 32 && p.d % 64 == 0 && p.d_e % 8 == 0 &&
+         ntok < (size_t{1} << 30) && ncb * p.B * 128 * sizeof(float) < (size_t{1} << 31) &&
+         ((reinterpret_cast<uintptr_t>(p.h) | reinterpret_cast<uintptr_t>(p.W1) | reinterpret_cast<uintptr_t>(p.W_r) |
+           reinterpret_cast<uintptr_t>(p.E)) & 15) == 0;
+}
+// Whether a call with all the workspace it asks for runs in the two-kernel form.
+inline bool route_uses_tiles(const RouteParams& p, bool bf16) {
+  return !route_one_kernel_ok(p, bf16) || static_cast<size_t>(p.B) * p.T <= kRouteTileMaxTok;
 }
 hipError_t launch_route(const RouteParams& p, bool bf16, hipStream_t s);
 hipError_t launch_select(const RouteParams& p, hipStream_t s);

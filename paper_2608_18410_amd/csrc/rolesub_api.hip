@@ -228,7 +228,29 @@ hipError_t run_tiles(RouteParams p, bool bf16, void* workspace, size_t bytes, hi
 // leave room for partial products.
 hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes, bool split, hipStream_t s) {
   const RouteWs w = route_ws(p.B, p.T, p.d, p.G, p.C, p.Hr, p.kind);
-  if (!route_uses_tiles(p, bf16)) {
+  // A launch holds fewer than 2^24 workgroups of 256 threads (HIP drops the rest
+  // without an error): pooling blocks and language-term rows of half of that.
+  const int per = std::max((p.d + 255) / 256, ((p.kind == 0 ? p.Hr : p.G) + 7) / 8);
+  int nb = std::min(p.B, std::max(1, (1 << 23) / per));
+  bool one = !route_uses_tiles(p, bf16);
+  if (!one && !split) {
+    const size_t fold = route_fold_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float);
+    if (route_one_kernel_ok(p, bf16)) {
+      // Where the array does not hold the products of all tokens, the single kernel
+      // takes less than ranges or several launches, in the same bits: d = 4096, 330
+      // samples of 9 tokens 67.8 us against 76.1, 250 of 12 62.2 against 73.2.
+      const int MB = route_tile_blocks(p.Hr, p.G, p.C, p.kind), S = route_tile_slices(p.d, MB, p.kind, bf16);
+      const size_t tiles = (static_cast<size_t>(p.B) * p.T + 63) / 64;
+      one = w.off_s + fold + tiles * S * MB * 4096 > ws_bytes;
+    } else {
+      // room for the folded operands and the partial products of one tile at least
+      // (2.2 MiB hold those of any router, see route_tile_smax; with one sample
+      // everything takes less than 7.5 MiB, since d + 2 Hr <= 16384)
+      const size_t room = fold + (size_t{9} << 18);
+      while (nb > 1 && route_ws(nb, p.T, p.d, p.G, p.C, p.Hr, p.kind).off_s + room > ws_bytes) nb = (nb + 1) / 2;
+    }
+  }
+  if (one) {
     char* ws = static_cast<char*>(workspace);
     p.cb = reinterpret_cast<float*>(ws);
     p.F = reinterpret_cast<float*>(ws + w.off_F);
@@ -238,17 +260,6 @@ hipError_t run_route(RouteParams p, bool bf16, void* workspace, size_t ws_bytes,
     p.rcnt = split ? reinterpret_cast<int*>(ws + w.off_c) : nullptr;
     p.sk_polls = route_sk_polls();
     return launch_route(p, bf16, s);
-  }
-  // A launch holds fewer than 2^24 workgroups of 256 threads (HIP drops the rest
-  // without an error): pooling blocks and language-term rows of half of that.
-  const int per = std::max((p.d + 255) / 256, ((p.kind == 0 ? p.Hr : p.G) + 7) / 8);
-  int nb = std::min(p.B, std::max(1, (1 << 23) / per));
-  if (!split) {
-    // room for the folded operands and the partial products of one tile at least
-    // (2.2 MiB hold those of any router, see route_tile_smax; with one sample
-    // everything takes less than 7.5 MiB, since d + 2 Hr <= 16384)
-    const size_t room = route_fold_floats(p.Hr, p.G, p.C, p.kind) * sizeof(float) + (size_t{9} << 18);
-    while (nb > 1 && route_ws(nb, p.T, p.d, p.G, p.C, p.Hr, p.kind).off_s + room > ws_bytes) nb = (nb + 1) / 2;
   }
   const size_t es = bf16 ? 2 : 4, T = static_cast<size_t>(p.T);
   size_t b0 = 0;

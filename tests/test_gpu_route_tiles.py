@@ -203,3 +203,22 @@ def test_split_k_matches_single_kernel_past_the_two_kernel_range(B, T, G, polls,
         for name in ("mask", "idx", "count", "scores"):
             assert torch.equal(r[name], a[name]), name
     assert bool(torch.isfinite(a["scores"]).all())
+
+
+@pytest.mark.parametrize("B,T", [(300, 1), (330, 2), (230, 12), (250, 12)])
+def test_route_noalloc_of_many_short_samples(B, T):
+    """Samples whose pooled states leave the array room for the products of all
+    tokens (300 x 1: two-kernel form) or not (the single kernel): the bits of the
+    call on a workspace, which runs the two-kernel form."""
+    d, G, C = 4096, 8, 8
+    w = synth.workload(2).replace(B=B, d=d, G=G, C=C, d_e=64, n_vis=T - T // 3, n_lang=T // 3, n_prop=0)
+    router = _router("mlp2", _weights(w, "mlp2", np.random.default_rng(B)), torch.bfloat16)
+    h = torch.randn((B, T, d), generator=torch.Generator(device=DEV).manual_seed(B), device=DEV).bfloat16()
+    types = put_u8(np.broadcast_to(w.types(), (B, T)).copy())
+    budget = rs.make_budget(rs.TOPK, (4, 6, G, G))
+    print(f"route_noalloc, {B} samples of {T}", flush=True)
+    a = rs.route(types, budget, G, h=h, router=router, out=_outs(B, T, G))
+    b = rs.route_noalloc(types, budget, G, h=h, router=router, out=_outs(B, T, G))
+    torch.cuda.synchronize()
+    for n in ("mask", "idx", "count", "scores"):
+        assert torch.equal(a[n], b[n])
